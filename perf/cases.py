@@ -368,9 +368,9 @@ def work(case):
 
 
 def tolerance(case):
-    """Attention: bf16 results and bf16 probabilities under fp32 sums; both give 2.3e-3 against
-    the 64-bit result. Row statistics: fp32 sums of V exponentials, 2e-7 off it. A token drawn where the
-    cumulative sum meets the threshold may differ by the rounding of the row's sum."""
+    """Attention: bf16 results and bf16 probabilities under fp32 sums, measured 2.3e-3 off the
+    64-bit result. Row statistics: fp32 sums of V exponentials, measured up to 2e-7 off. A token
+    drawn where the cumulative sum meets the threshold may differ by the rounding of the sum."""
     op = case["op"]
     if op in ("prepare", "append") or (op == "accept" and (case["probs"] or case["temperature"] == 0)):
         return "exact"
