@@ -361,9 +361,11 @@ def work(case):
         flops += 4 * d * Hq * K * (L / R + K / R / 2)
     if op in ("accept", "drafter", "round"):
         row = case["V"] * (4 if case["dtype"] == "f32" else 2)
-        drafts = 0 if case["temperature"] == 0 else N - R if op == "drafter" else K - R
-        nbytes += (K + drafts) * row
-        flops += 4 * (K + drafts) * case["V"]
+        rows = K if case["temperature"] == 0 else K + (N - R if op == "drafter" else K - R)
+        if case.get("probs"):  # a probability row is read at its drafted token; one pair of rows is drawn from
+            rows = 2 * R
+        nbytes += rows * row
+        flops += 4 * rows * case["V"]
     return {"bytes": nbytes, "flops": flops}
 
 
