@@ -71,17 +71,13 @@ __device__ inline V stream_load(const V* p) {
     return __builtin_nontemporal_load(p);
 }
 
-// fp32 probability of token v of a row: softmax(l / T) from its (max m, 1/sum) in logits
-// mode, 2^(l * (log2e / T) - m * log2e) * (1/sum) with one fused multiply-add before the
-// exponent; the stored value in probability mode. The draw's weights (weight_xy) compute
+// fp32 probability of a token from its stored value x and its row's (max m, 1/sum): softmax(l / T)
+// in logits mode, 2^(l * (log2e / T) - m * log2e) * (1/sum) with one fused multiply-add before
+// the exponent; the stored value in probability mode. The draw's weights (residual_xy) compute
 // the same expression.
-template <bool LOGITS, typename T>
-__device__ inline float prob_of(const T* row, int v, float m, float iS, float invT) {
-    if (LOGITS) {
-        return __builtin_amdgcn_exp2f(__builtin_fmaf(load_x<T>(row, v), invT * kLog2e, -m * kLog2e)) * iS;
-    } else {
-        return load_x<T>(row, v);
-    }
+template <bool LOGITS>
+__device__ inline float prob_of(float x, float m, float iS, float invT) {
+    return LOGITS ? __builtin_amdgcn_exp2f(__builtin_fmaf(x, invT * kLog2e, -m * kLog2e)) * iS : x;
 }
 
 // floor(min(r, 1) * 2^40) for r > 0 (0 for r <= 0 or NaN). v = min(r, 1) * 2^40 is exact
@@ -96,6 +92,22 @@ __device__ inline uint64_t weight_of(float r) {
     const float lf = v - hf * 4294967296.0f;
     return ((uint64_t)(uint32_t)hf << 32) | (uint64_t)(uint32_t)lf;
 }
+
+// Running sum of up to 2^12 weights floor(min(r, 1) * 2^40) as the sums of their upper 21 and
+// lower 20 bits in two 32-bit registers: floor(r 2^20), and the remainder's next 20 bits (both
+// scalings are exact). Six vector operations a weight, where a 64-bit sum of weight_of takes ten;
+// the draw's chunk sums are bound by these at many requests.
+struct WeightSum {
+    uint32_t hi = 0, lo = 0;
+    __device__ inline void add(float r) {
+        r = r > 0.0f ? r : 0.0f;
+        r = r < 1.0f ? r : 1.0f;
+        const float v = r * 1048576.0f;
+        hi += (uint32_t)v;
+        lo += (uint32_t)(__builtin_amdgcn_fractf(v) * 1048576.0f);
+    }
+    __device__ inline uint64_t total() const { return ((uint64_t)hi << 20) + lo; }
+};
 
 template <typename T>
 __device__ inline const T* row_ptr(const void* base, long long row, int V) {
@@ -231,25 +243,28 @@ __global__ __launch_bounds__(kThreads) void rowstats_kernel(AcceptArgs a) {
     if (threadIdx.x == 0) dst[c] = st;
 }
 
-// combine the per-chunk (max, sum) of one row; chunk statistics are loaded 8 at a time
-// so their latencies overlap
+// combine the per-chunk (max, sum) of one row; chunk statistics are loaded 16 at a time so
+// their latencies overlap, and joined 8 at a time
 __device__ inline void merge_stats_ms(const float2* st, int NC, float& m, float& Sum) {
     float mm = -INFINITY, S = 0.0f;
-    for (int c0 = 0; c0 < NC; c0 += 8) {
-        float2 v[8];
+    for (int c0 = 0; c0 < NC; c0 += 16) {
+        float2 v[16];
 #pragma unroll
-        for (int k = 0; k < 8; k++) v[k] = c0 + k < NC ? st[c0 + k] : make_float2(-INFINITY, 0.0f);
-        float bm = mm;
+        for (int k = 0; k < 16; k++) v[k] = c0 + k < NC ? st[c0 + k] : make_float2(-INFINITY, 0.0f);
 #pragma unroll
-        for (int k = 0; k < 8; k++) bm = fmaxf(bm, v[k].x);
-        if (bm != -INFINITY) {
-            float acc = S * __builtin_amdgcn_exp2f((mm - bm) * kLog2e);
-            if (mm == -INFINITY) acc = 0.0f;
+        for (int h = 0; h < 16; h += 8) {
+            float bm = mm;
 #pragma unroll
-            for (int k = 0; k < 8; k++)
-                if (v[k].x != -INFINITY) acc += v[k].y * __builtin_amdgcn_exp2f((v[k].x - bm) * kLog2e);
-            S = acc;
-            mm = bm;
+            for (int k = h; k < h + 8; k++) bm = fmaxf(bm, v[k].x);
+            if (bm != -INFINITY) {
+                float acc = S * __builtin_amdgcn_exp2f((mm - bm) * kLog2e);
+                if (mm == -INFINITY) acc = 0.0f;
+#pragma unroll
+                for (int k = h; k < h + 8; k++)
+                    if (v[k].x != -INFINITY) acc += v[k].y * __builtin_amdgcn_exp2f((v[k].x - bm) * kLog2e);
+                S = acc;
+                mm = bm;
+            }
         }
     }
     m = mm;
@@ -272,6 +287,13 @@ __device__ inline void merge_stats(const float2* st, int NC, float& m, float& iS
 // ----------------------------------------------------------------------------------
 template <bool LOGITS, typename T>
 __device__ inline ReqPlan decide_req(const AcceptArgs& a, const int i, const int lane, const bool write) {
+    // the drafted tokens and uniforms first: the gathers of the tests' logits depend on them
+    int d = -1;
+    float u_t = 0.0f;
+    if (lane < a.D) {
+        d = a.tokens[(size_t)i * a.D + lane];
+        u_t = a.ua[(size_t)i * a.D + lane];
+    }
     const int q0 = a.qo[i];
     const int n = a.qo[i + 1] - q0 - 1;
     const int K = a.qo[a.R];
@@ -288,6 +310,12 @@ __device__ inline ReqPlan decide_req(const AcceptArgs& a, const int i, const int
             for (int t = lane; t < a.b; t += 64) a.out_tokens[(size_t)i * a.b + t] = -1;
         }
         return pl;
+    }
+    // what the test of draft t+1 reads in lane t, ahead of the statistics' merge
+    float x_t = 0.0f, y_t = 0.0f;
+    if (lane < n && d >= 0 && d < a.V) {
+        x_t = load_x<T>(row_ptr<T>(a.target, q0 + lane, a.V), d);
+        y_t = load_x<T>(row_ptr<T>(a.draft, (long long)i * a.D + lane, a.V), d);
     }
     // per-row softmax statistics: lane r -> P_r (r <= n), lane 32+t -> Q_{t+1} (t < n)
     float m = 0.0f, iS = 0.0f;
@@ -307,16 +335,14 @@ __device__ inline ReqPlan decide_req(const AcceptArgs& a, const int i, const int
     const float mPt = __shfl(m, lane & 31, 64), iSPt = __shfl(iS, lane & 31, 64);
     const float mQt = __shfl(m, 32 + (lane & 31), 64), iSQt = __shfl(iS, 32 + (lane & 31), 64);
     bool reject = false, bad_tok = false;
-    int d = -1;
     if (lane < n) {
-        d = a.tokens[(size_t)i * a.D + lane];
         if (d < 0 || d >= a.V) {
             reject = true;
             bad_tok = true;
         } else {
-            const float p = prob_of<LOGITS, T>(row_ptr<T>(a.target, q0 + lane, a.V), d, mPt, iSPt, a.invT);
-            const float q = prob_of<LOGITS, T>(row_ptr<T>(a.draft, (long long)i * a.D + lane, a.V), d, mQt, iSQt, a.invT);
-            const double u = (double)a.ua[(size_t)i * a.D + lane];
+            const float p = prob_of<LOGITS>(x_t, mPt, iSPt, a.invT);
+            const float q = prob_of<LOGITS>(y_t, mQt, iSQt, a.invT);
+            const double u = (double)u_t;
             reject = !(u * (double)q < (double)p);
             if (write && a.dbg_pq) {  // diagnostics: the values this test compared
                 a.dbg_pq[(size_t)i * a.D + lane] = p;
@@ -356,7 +382,11 @@ __device__ inline ReqPlan decide_req(const AcceptArgs& a, const int i, const int
 
 
 template <bool LOGITS>
-__device__ inline uint64_t weight_xy(const ReqPlan& pl, int col, float x, float y, float invT);
+__device__ inline float residual_xy(const ReqPlan& pl, int col, float x, float y, float invT);
+template <bool LOGITS>
+__device__ inline uint64_t weight_xy(const ReqPlan& pl, int col, float x, float y, float invT) {
+    return weight_of(residual_xy<LOGITS>(pl, col, x, y, invT));
+}
 
 // weight of token v in column col (see weight_xy), loading the values itself
 template <bool LOGITS, typename T>
@@ -366,18 +396,16 @@ __device__ inline uint64_t weight_at(const AcceptArgs& a, const ReqPlan& pl, int
     return weight_xy<LOGITS>(pl, col, x, y, a.invT);
 }
 
-// weight of one token from already loaded values x (target) and y (draft): column 0 is
-// the residual (or bonus) weight, column 1 the fallback weight of P_a
+// what the weight of one token is taken of, from already loaded values x (target) and y
+// (draft): column 0 is the residual (or bonus) probability, column 1 the fallback P_a
 template <bool LOGITS>
-__device__ inline uint64_t weight_xy(const ReqPlan& pl, int col, float x, float y, float invT) {
+__device__ inline float residual_xy(const ReqPlan& pl, int col, float x, float y, float invT) {
     // the probability of prob_of, with the row's constants hoisted out of the token loop
     const float c = invT * kLog2e;
     const float pv = LOGITS ? __builtin_amdgcn_exp2f(__builtin_fmaf(x, c, -pl.mP * kLog2e)) * pl.iSP : x;
-    if (pl.mode != 0 || col == 1) return weight_of(pv);
+    if (pl.mode != 0 || col == 1) return pv;
     const float qv = LOGITS ? __builtin_amdgcn_exp2f(__builtin_fmaf(y, c, -pl.mQ * kLog2e)) * pl.iSQ : y;
-    float r = pv - qv;
-    if (!(r > 0.0f)) r = 0.0f;
-    return weight_of(r);
+    return pv - qv;  // (the weight of a negative or NaN difference is 0)
 }
 
 // Sum of one weight column over the contiguous range [lo, hi) of the vocabulary
@@ -388,17 +416,17 @@ __device__ inline uint64_t range_sum(const AcceptArgs& a, const ReqPlan& pl, int
     const T* prow = row_ptr<T>(a.target, pl.rowP, a.V);
     const bool need_q = pl.mode == 0 && col == 0;
     const T* qrow = need_q ? row_ptr<T>(a.draft, pl.rowQ, a.V) : prow;
-    uint64_t sum = 0;
+    WeightSum sum;
     int v = lo;
     for (; v + N <= hi; v += N) {
         const typename Vec<T>::type xp = *(const uvec*)(prow + v);
         typename Vec<T>::type xq = xp;
         if (need_q) xq = *(const uvec*)(qrow + v);
 #pragma unroll
-        for (int e = 0; e < N; e++) sum += weight_xy<LOGITS>(pl, col, to_f(xp[e]), to_f(xq[e]), a.invT);
+        for (int e = 0; e < N; e++) sum.add(residual_xy<LOGITS>(pl, col, to_f(xp[e]), to_f(xq[e]), a.invT));
     }
-    for (; v < hi; v++) sum += weight_xy<LOGITS>(pl, col, load_x<T>(prow, v), load_x<T>(qrow, v), a.invT);
-    return sum;
+    for (; v < hi; v++) sum.add(residual_xy<LOGITS>(pl, col, load_x<T>(prow, v), load_x<T>(qrow, v), a.invT));
+    return sum.total();
 }
 
 // One thread's full range of kResPer tokens: every load is issued before any weight is
@@ -427,13 +455,22 @@ __device__ inline void range_load(const AcceptArgs& a, const ReqPlan& pl, int co
 
 template <bool LOGITS, typename T>
 __device__ inline uint64_t range_regs_sum(const AcceptArgs& a, const ReqPlan& pl, int col, const RangeRegs<T>& g) {
-    uint64_t sum = 0;
+    WeightSum sum;
+    // (the choice of column and row pair is the same for all tokens: one branch, not a select each)
+    if (pl.mode != 0 || col == 1) {
 #pragma unroll
-    for (int k = 0; k < RangeRegs<T>::NV; k++)
+        for (int k = 0; k < RangeRegs<T>::NV; k++)
 #pragma unroll
-        for (int e = 0; e < RangeRegs<T>::VEC; e++)
-            sum += weight_xy<LOGITS>(pl, col, to_f(g.xp[k][e]), to_f(g.xq[k][e]), a.invT);
-    return sum;
+            for (int e = 0; e < RangeRegs<T>::VEC; e++)
+                sum.add(residual_xy<LOGITS>(pl, 1, to_f(g.xp[k][e]), 0.0f, a.invT));
+    } else {
+#pragma unroll
+        for (int k = 0; k < RangeRegs<T>::NV; k++)
+#pragma unroll
+            for (int e = 0; e < RangeRegs<T>::VEC; e++)
+                sum.add(residual_xy<LOGITS>(pl, 0, to_f(g.xp[k][e]), to_f(g.xq[k][e]), a.invT));
+    }
+    return sum.total();
 }
 
 __device__ inline uint64_t wave_incl_scan_u64(uint64_t v, int lane) {
