@@ -202,7 +202,7 @@ typedef struct {
     int32_t max_kv_len;        /* upper bound of kv_lens[i], <= 2^22                  */
     int32_t dtype;             /* sv_dtype of q, caches and out                       */
     float sm_scale;            /* logit scale; 0 means 1/sqrt(d)                      */
-    int32_t kv_split;          /* tokens per split-KV work item (multiple of 64), 0 = auto */
+    int32_t kv_split;          /* tokens per work item (multiple of 64), 0 = auto */
 } sv_attn_desc;
 
 /*
@@ -220,8 +220,8 @@ typedef struct {
  * qo_indptr  [R+1] int32 (1 <= k_i <= block), kv_lens [R] int32 (k_i <= kv_lens[i] <= max_kv_len)
  * out        [total_q_max, Hq, d] same dtype as q;  lse [total_q_max, Hq] fp32 or NULL
  * ws         scratch of at least sv_verify_attn_workspace_size(desc) bytes (bf16:
- *            the work list of the persistent kernel and the partial results of
- *            split-KV work items; fp32: none), device memory, overwritten by every call.
+ *            the work plan of the persistent kernel and the partial results of
+ *            contexts cut into several work items; fp32: none), device memory, overwritten by every call.
  * bf16 runs on MFMA with fp32 accumulation; fp32 runs on vector ALUs in fp32.
  */
 sv_status sv_verify_attn(const sv_attn_desc* desc, const void* q, const void* k_cache,
@@ -232,8 +232,8 @@ size_t sv_verify_attn_workspace_size(const sv_attn_desc* desc);
 
 /*
  * sv_verify_attn_plan and sv_verify_attn_run -- sv_verify_attn in two parts: the bf16
- * path's work plan (which (request, kv-head, split, row block) items exist, largest
- * first) depends only on the descriptor, qo_indptr and kv_lens, so a round builds it once
+ * path's work plan (how the (request, kv-head, row block) units are divided among the
+ * workgroups) depends only on the descriptor, qo_indptr and kv_lens, so a round builds it once
  * and every attention layer of that round runs on it, as serving engines plan a batch
  * once per step (Sec. 4.2: one packed verify batch per round, evaluated by every layer
  * of the target model).

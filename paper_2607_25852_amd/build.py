@@ -21,7 +21,8 @@ BUILD_DIR = os.path.join(HERE, "_build")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
-SOURCES = ["sv_api.cpp", "sv_host.cpp", "budget.hip", "accept.hip", "attn.hip", "pack.hip"]
+SOURCES = ["sv_api.cpp", "sv_host.cpp", "budget.hip", "accept.hip", "attn.hip",
+           "attn_list.hip", "pack.hip"]
 PROBE_SOURCES = ["read_probe.hip"]
 COMMON = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-I" + INC, "-I" + CSRC,
           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]

@@ -1,123 +1,81 @@
 // Verify attention over a paged KV cache (AngelSpec Sec. 4.1: every kept block
 // position is evaluated by the target model; Sec. 4.2: one dense packed batch).
 //
-// bf16 path (MFMA). A workgroup owns one (request i, kv-head h, split s) work item:
-// the G*k_i query rows of that kv-head group against tokens [s*split, (s+1)*split)
-// of the request's context. Query rows go on the N side of the MFMA and KV tokens
+// bf16 path (MFMA), for fewer than two (request, kv-head, row block) units per compute unit; from
+// there on a list of items does as well or better (attn_list.hip). The plan (attn_plan.h) cuts the line of all (request, row block) units
+// of a kv-head into ranges by cost; a workgroup takes one range of one head at a time and
+// processes its pieces: the query rows of a unit against a run of 64-token tiles of the
+// request's context. Query rows go on the N side of the MFMA and KV tokens
 // on the M side, so S^T = K Q^T puts all scores of one query row in one lane pair:
 // the online-softmax max/sum is lane-local plus one cross-half swap. The P^T
 // fragment is then already in the B-operand layout of O^T = V^T P^T; V is staged
 // transposed in LDS to serve the A operand. K and V tiles of 64 tokens are
-// gathered through the page table into double-buffered LDS while the previous
-// tile is multiplied. Work items whose split lies past the request's length exit
-// at once; requests with more than one split write fp32 partials merged by a
-// second kernel (log-sum-exp weights).
+// gathered through the page table into an LDS ring while earlier tiles are multiplied.
+// A unit that lies in one range is written directly; the pieces of a cut unit leave fp32
+// partials merged by a second kernel (log-sum-exp weights).
+//
+// Bound by the K/V stream up to 64 rows per kv-head group (7.0 of the 7.1 TB/s a plain read
+// reaches while a workgroup streams), by the softmax's vector work in whole-tile units; the rest
+// is the pieces' starts and, before, the uneven end. Measured against the sorted list of
+// attn_list.hip: 4 MTP requests (188 MB) 44.1 -> 41 us, 27 requests on pages of 16 (256 MB)
+// 65 -> 54 us, 32 requests of 65536..131072 tokens (6.45 GB) 1333 -> 1228 us.
 //
 // fp32 path (vector ALU): one workgroup per (query row, head); its four waves take
 // interleaved 64-key tiles and merge their softmax states at the end.
+#include <algorithm>
 #include <atomic>
+#include <type_traits>
 
 #include "attn_plan.h"
+#include "attn_tile.h"
 #include "sv_internal.h"
 
 namespace sv {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
-
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-constexpr int kTile = 64;  // KV tokens per pipeline step
-static_assert(kTile == kAttnTile, "the work plan counts tiles of the kernel's size");
-
-struct AttnArgs {
-    const void* q;
-    const void* kc;
-    const void* vc;
-    const int32_t* page_table;
-    const int32_t* qo;
-    const int32_t* kv_lens;
-    void* out;
-    float* lse;
-    float* part_o;    // [max_splits, total_q_max, Hq, d]
-    float* part_lse;  // [max_splits, total_q_max, Hq]  (log2 domain)
-    int R, total_q, Hq, Hkv, G, block;
-    int log2P, maxp, num_pages, max_kv_len;
-    int split, max_splits, nrb;  // nrb: row blocks (16 rows per wave) per (request, kv-head)
-    int max_items;               // R * max_splits * Hkv * nrb (capped at INT_MAX): the longest work list
-    float scale_log2;  // sm_scale * log2(e)
-    float scale;       // sm_scale
+struct RangeArgs : AttnArgs {
+    int ranges, slot_rows;  // most ranges per head, rows of a partial result
 };
-
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
-
-// round-to-nearest-even fp32 -> bf16 bits
-__device__ inline uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x7FFFFFu)) return 0x7FC0;
-    u += 0x7FFFu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
-}
+static_assert(kPlanGrid == kAttnItems && sizeof(AttnRange) == 32, "the host sizes the plan");
 
 // ---------------------------------------------------------------------------------
 // bf16 MFMA kernel
 // ---------------------------------------------------------------------------------
-// ---------------------------------------------------------------------------------
-// LDS tile layout: a 64-token tile of K and of V, each [token][HD] bf16, rows of HD*2
-// bytes with their 16-byte chunks XOR-swizzled: logical chunk c of token t sits at
-// position c ^ swz(t). swz swaps the two 2-bit fields of t % 16 so that (a) the 16
-// rows read together by one quarter-wave of the K-operand loads hit 16 different chunk
-// positions and (b) the 4 rows x 4 chunks read by one half-wave of the transpose reads
-// (two 16-lane groups) do too.
-// ---------------------------------------------------------------------------------
-__device__ __host__ inline int swz(int t) { return ((t & 3) << 2) | ((t >> 2) & 3); }
+// How a tile's K/V addresses are found (by page size): one page holds the whole tile, one
+// page holds each 1 KB DMA segment of it, or every lane looks its token's page up.
+enum class PageMode { kTile, kSegment, kLane };
 
 template <int HD, int NBUF>
 struct LdsRing {
     static constexpr int kTileBytes = kTile * HD * 2;  // one tensor
     static constexpr int kMaxSlots = 1024;              // page-table entries of one split
-    uint16_t kv[NBUF][2][kTile * HD];                   // [buffer][K=0/V=1][token*HD + d]
+    uint16_t k[NBUF][kTile * HD];                       // [buffer][token*HD + d]
+    uint16_t v[NBUF][kTile * HD];
     int32_t pid[kMaxSlots];
 };
 
-// Asynchronous 16-byte-per-lane copy global -> LDS: lane l's 16 bytes land at
-// lds_base + 16*l. Issued from inline assembly so the compiler does not drain it
-// before every LDS read; completion is awaited explicitly with wait_vm<N>(). The
-// loads carry the non-temporal hint: every K/V byte is read by one workgroup once,
-// so keeping it in L2 and the last-level cache only evicts lines that are reused.
-__device__ inline void dma16(const void* gptr, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(gptr), "s"(lds_base)
-                 : "memory", "m0");
-}
-// Same copy with a wave-uniform 64-bit base in SGPRs and a 32-bit per-lane byte offset.
-__device__ inline void dma16s(uint32_t voff, const void* sbase, uint32_t lds_base) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(sbase),
-                 "s"(lds_base)
-                 : "memory", "m0");
-}
-template <int N>
-__device__ inline void wait_vm() {
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+// wait until at most min(newer, MAX) tiles of IPW loads each are outstanding
+template <int MAX, int IPW>
+__device__ inline void wait_tiles(int newer) {
+    if constexpr (MAX == 0) {
+        wait_vm<0>();
+    } else {
+        if (newer >= MAX) wait_vm<MAX * IPW>();
+        else wait_tiles<MAX - 1, IPW>(newer);
+    }
 }
 
-typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef short i16x8 __attribute__((ext_vector_type(8)));
-typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
-
-// One work item (request i, kv-head h, split s, up to (NW/HALVES)*32 query rows from row0
-// of the kv-head group). NBUF-deep LDS ring:
+// One piece of a unit (request i, kv-head h, up to (NW/HALVES)*32 query rows from row0 of
+// the kv-head group): tiles t0 .. t1-1 of the nt tiles of its context. slot: its partial
+// result when the unit is cut (t1 - t0 < nt). NBUF-deep LDS ring:
 // tile t is multiplied while tiles t+1 .. t+NBUF-1 stream in. HALVES == 2: wave w owns
 // query rows 32*(w/2) .. +31 of the row block and token half w%2 of every tile (so a
 // 64-row group keeps all four SIMDs busy, two waves each); the two halves of a row group
 // merge their softmax states at the end. HALVES == 1: wave w owns rows 32*w .. +31 over
-// the whole tile (256 rows per workgroup). Every early return is uniform over the
-// workgroup.
-template <int HD, int NW, int NBUF, bool ONEPAGE, int HALVES>
-__device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& lds, int i, int h, int s, int row0) {
+// the whole tile (256 rows per workgroup).
+template <int HD, int NW, int NBUF, PageMode PM, int HALVES>
+__device__ __forceinline__ void attn_item(const RangeArgs& a, LdsRing<HD, NBUF>& lds, int i, int h, int row0, int q0,
+                                          int k_i, int kv_len, int t0, int t1, int nt, int slot) {
     constexpr int CPR = HD / 8;             // 16-byte chunks per token row
     constexpr int TPS = 1024 / (HD * 2);    // tokens per 1 KB DMA segment
     constexpr int NSEG = kTile / TPS;       // segments per tensor per tile
@@ -135,29 +93,21 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
     const int lane = tid & 63, w = tid >> 6;
-    const int q0 = a.qo[i];
-    const int k_i = a.qo[i + 1] - q0;
-    int kv_len = a.kv_lens[i];
-    if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
     const int L = kv_len - k_i;
-    // (bitwise or: both descriptor loads are issued before the test)
-    if ((k_i <= 0) | (k_i > a.block) | (L < 0) | (q0 < 0) | (q0 + k_i > a.total_q)) return;
-    const int tok_begin = s * a.split;
-    if (tok_begin >= kv_len) return;
-    const int tok_end = min(kv_len, tok_begin + a.split);
-    const int nsplit = (kv_len + a.split - 1) / a.split;
+    const int p_begin = t0 * kTile;                    // tokens of the piece
+    const int p_end = min(kv_len, t1 * kTile);
     constexpr int RB = (NW / HALVES) * 32;    // query rows this mapping covers
-    const int M = min(a.G * k_i - row0, RB);  // rows of this item
-    if (M <= 0) return;
+    const int M = min(a.G * k_i - row0, RB);  // rows of this item (at least 1)
 
-    // page ids of this split -> LDS (the host keeps a split within 1024 pages). The first
-    // page id of each thread is loaded before the query fragments and stored after them,
-    // so the two round trips overlap.
-    const int slot0 = tok_begin >> a.log2P;
-    const int nslots = ((tok_end - 1) >> a.log2P) - slot0 + 1;
+    // The page ids of at most kMaxSlots pages are staged in LDS at a time; a piece over more
+    // pages is walked in chunks of whole tiles. The first page id of each thread is loaded
+    // before the query fragments and stored after them, so the two round trips overlap.
     const int32_t* __restrict__ pt = a.page_table + (size_t)i * a.maxp;
+    constexpr int kMaxSlots = LdsRing<HD, NBUF>::kMaxSlots;
+    const int chunk_tiles = max(1, ((kMaxSlots - 2) << a.log2P) / kTile);
+    int slot0 = p_begin >> a.log2P;
     int pg0 = -1;
-    if (tid < nslots && slot0 + tid < a.maxp) pg0 = pt[slot0 + tid];
+    if (slot0 + tid < a.maxp) pg0 = pt[slot0 + tid];
 
     // this lane's query row (N index of the MFMA) and its half (K-slice selector)
     // row group; token half of each tile (HALVES == 2), else the whole tile
@@ -169,7 +119,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
     const int jq = rr / a.G;
     const int head = h * a.G + rr % a.G;
     const int limit = L + jq;  // last visible key of this row (inclusive)
-    const int last_key = min(limit, tok_end - 1);  // ... and of this split
+    const int last_key = min(limit, p_end - 1);  // ... and of this piece
 
     // Per-lane element offsets of the V^T transpose reads inside a tile's V buffer: read
     // (qh, d-tile t) of 16-token k-chunk c lies at 16c*HD + vofs[qh][t] (for half-tile waves
@@ -202,12 +152,6 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
             qf[kk] = __builtin_bit_cast(bf16x8, v);
         }
     }
-    if (tid < nslots) lds.pid[tid] = (pg0 >= 0 && pg0 < a.num_pages) ? pg0 : -1;
-    for (int e = tid + NW * 64; e < nslots; e += NW * 64) {
-        const int slot = slot0 + e;
-        const int pg = slot < a.maxp ? pt[slot] : -1;
-        lds.pid[e] = (pg >= 0 && pg < a.num_pages) ? pg : -1;
-    }
     // the query fragments must have landed before the DMA ring starts: a wait the
     // compiler sees (vmcnt(0)) keeps it from re-checking them inside the loop, where
     // a vmcnt(0) would also drain the ring
@@ -219,48 +163,70 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
 
     const size_t head_off = (size_t)h << a.log2P;
     const int pmask = (1 << a.log2P) - 1;
-    const uint32_t lds_ring = (uint32_t)(uintptr_t)&lds.kv[0][0][0];
-    __syncthreads();  // page ids visible
-
     // DMA of one tile: wave w issues segments w*IPW .. w*IPW+IPW-1 of the 2*NSEG
     // (K segments first, then V). Lane l of a segment moves token row t = seg*TPS + l/CPR,
     // position l%CPR, fetching logical chunk (l%CPR) ^ swz(t); the per-lane byte offset of
-    // that chunk inside the tile is loop-invariant.
-    // ONEPAGE (page size >= 64): a 64-token tile lies inside one page, so each tile needs
-    // one wave-uniform base address; an invalid page reads page 0 (always present).
-    // Otherwise every lane looks its page up; tokens past the split end or on an invalid
-    // page read the first element of the cache. Either way such tokens are masked out of
-    // the scores and zeroed in the V operand.
+    // that chunk inside the tile (or segment) is loop-invariant.
+    // Tile and segment pages need one wave-uniform base address each; an invalid page, or a
+    // segment past the piece's end, reads page 0 (always present). Per-lane look-up: tokens
+    // past the end or on an invalid page read the first element of the cache. Either way such
+    // tokens are masked out of the scores and zeroed in the V operand.
     uint32_t voff[IPW], ldsoff[IPW];
-    int tk[IPW];
+    int tk[IPW], sg[IPW];
 #pragma unroll
     for (int k = 0; k < IPW; k++) {
         const int n = w * IPW + k;
         const int seg = n % NSEG;
         const int t = seg * TPS + lane / CPR;
         tk[k] = t;
-        voff[k] = (uint32_t)(t * HD + (((lane % CPR) ^ (swz(t) & (CPR - 1))) << 3)) * 2u;
-        ldsoff[k] = (uint32_t)__builtin_amdgcn_readfirstlane((n / NSEG) * LdsRing<HD, NBUF>::kTileBytes + seg * 1024);
+        sg[k] = __builtin_amdgcn_readfirstlane(seg * TPS);
+        voff[k] = (uint32_t)((PM == PageMode::kSegment ? lane / CPR : t) * HD + (((lane % CPR) ^ (swz(t) & (CPR - 1))) << 3)) * 2u;
+        ldsoff[k] = (uint32_t)__builtin_amdgcn_readfirstlane(seg * 1024);
     }
+    constexpr int TB = LdsRing<HD, NBUF>::kTileBytes;
     const int my_tensor = __builtin_amdgcn_readfirstlane((w * IPW) / NSEG);  // a wave moves one tensor
     const uint16_t* cbase = my_tensor ? vcp : kcp;
-    auto issue_tile = [&](int tile, int buf) {
-        const int tb = tok_begin + tile * kTile;
-        const uint32_t lbuf = lds_ring + (uint32_t)(buf * 2 * LdsRing<HD, NBUF>::kTileBytes);
-        if constexpr (ONEPAGE) {
-            const int pg = __builtin_amdgcn_readfirstlane(lds.pid[(tb >> a.log2P) - slot0]);
+    const uint32_t my_ring = (uint32_t)(uintptr_t)(my_tensor ? &lds.v[0][0] : &lds.k[0][0]);
+    int ibuf = 0;  // the buffer of this wave's tensor that the next issued tile goes to
+    // The page ids of a tile are read from LDS (find_pages) one step before its DMA is issued
+    // (issue_tile), so the look-up's latency is off the path from barrier to barrier.
+    constexpr int NPG = PM == PageMode::kTile ? 1 : IPW;
+    int pgv[NPG];
+    auto find_pages = [&](int tile) {
+        const int tb = p_begin + tile * kTile;
+#pragma unroll
+        for (int k = 0; k < NPG; k++) {
+            const int tok = PM == PageMode::kTile ? tb : tb + (PM == PageMode::kSegment ? sg[k] : tk[k]);
+            pgv[k] = lds.pid[min((tok >> a.log2P) - slot0, kMaxSlots - 1)];
+        }
+    };
+    auto issue_tile = [&](int tile) {
+        const int tb = p_begin + tile * kTile;
+        const uint32_t lbuf = my_ring + (uint32_t)(ibuf * TB);
+        ibuf = ibuf + 1 == NBUF ? 0 : ibuf + 1;
+        if constexpr (PM == PageMode::kTile) {
+            const int pg = __builtin_amdgcn_readfirstlane(pgv[0]);
             const uint16_t* base = pg >= 0
                 ? cbase + ((((size_t)pg * a.Hkv) << a.log2P) + head_off + (size_t)(tb & pmask)) * HD
                 : cbase + (size_t)(tb & pmask) * HD;
 #pragma unroll
             for (int k = 0; k < IPW; k++) dma16s(voff[k], base, lbuf + ldsoff[k]);
+        } else if constexpr (PM == PageMode::kSegment) {
+#pragma unroll
+            for (int k = 0; k < IPW; k++) {
+                const int tok = tb + sg[k];
+                const int pg = __builtin_amdgcn_readfirstlane(pgv[k]);
+                const uint16_t* base = pg >= 0 && tok < p_end
+                    ? cbase + ((((size_t)pg * a.Hkv) << a.log2P) + head_off + (size_t)(tok & pmask)) * HD
+                    : cbase + (size_t)(tok & pmask) * HD;
+                dma16s(voff[k], base, lbuf + ldsoff[k]);
+            }
         } else {
 #pragma unroll
             for (int k = 0; k < IPW; k++) {
                 const int tok = tb + tk[k];
-                const int pg = lds.pid[min((tok >> a.log2P) - slot0, nslots - 1)];
-                const uint16_t* src = (tok < tok_end && pg >= 0)
-                    ? cbase + ((((size_t)pg * a.Hkv) << a.log2P) + head_off + (size_t)(tok & pmask)) * HD
+                const uint16_t* src = (tok < p_end && pgv[k] >= 0)
+                    ? cbase + ((((size_t)pgv[k] * a.Hkv) << a.log2P) + head_off + (size_t)(tok & pmask)) * HD
                           + (voff[k] / 2 - tk[k] * HD)
                     : cbase;
                 dma16(src, lbuf + ldsoff[k]);
@@ -269,10 +235,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
     };
 
     constexpr int NSB = 2 / HALVES;  // 32-token halves of a tile handled by this wave
-    auto compute_tile = [&](int buf, int tb) {
-        if (rg * 32 >= M) return;
-        const uint16_t* kt = lds.kv[buf][0];
-        const uint16_t* vt = lds.kv[buf][1];
+    auto compute_tile = [&](const uint16_t* kt, const uint16_t* vt, int tb) {
         // S^T = K Q^T for each 32-token half this wave owns (unscaled), as two independent
         // accumulation chains: the two halves (whole-tile waves), or the even and odd
         // k-steps of one half. Each K fragment is read from LDS KPD MFMAs before the MFMA
@@ -320,7 +283,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
     #pragma unroll
             for (int sb = 0; sb < NSB; sb++) {
                 const int tb_h = tb + (HALVES == 2 ? th : sb) * 32;
-                if (tb_h + 31 > L || tb_h + 32 > tok_end) {
+                if (tb_h + 31 > L || tb_h + 32 > p_end) {
                     const int dlim = last_key - tb_h - 4 * half;  // mask where 8(e/4) + e%4 > dlim
     #pragma unroll
                     for (int e = 0; e < 16; e++)
@@ -363,7 +326,6 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
             // and output lane jl receives dim 32t + 16(g%2) + jl of tokens 16c + 8q + 4(g/2) +
             // 0..3. The operands are read VPD MFMAs ahead; the first VPD are in flight while the
             // exponents of the first half are computed.
-            const int g = lane >> 4, jl = lane & 15;
             constexpr int NJ = 2 * DT;    // PV MFMAs per 32-token half
             constexpr int NT = NSB * NJ;  // PV MFMAs per tile for this wave
             constexpr int VPD = 4;
@@ -426,10 +388,9 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
             l_run += ps0 + ps1;
         } else {
             // Half-tile waves: one online-softmax step per tile on the wave's half.
-            const int g = lane >> 4, jl = lane & 15;
             const int hh = th;
             const int tb_h = tb + hh * 32;
-            if (tb_h + 31 > L || tb_h + 32 > tok_end) {
+            if (tb_h + 31 > L || tb_h + 32 > p_end) {
                 const int dlim = last_key - tb_h - 4 * half;  // mask where 8(e/4) + e%4 > dlim
 #pragma unroll
                 for (int e = 0; e < 16; e++)
@@ -498,176 +459,276 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
     // pipeline: before multiplying tile t, wait until its DMA (and only its) is done,
     // barrier (tile t visible to all waves; tile t-1 no longer read), then refill the
     // buffer of tile t-1 with tile t+PF.
-    const int ntiles = (tok_end - tok_begin + kTile - 1) / kTile;
-#pragma unroll
-    for (int t = 0; t < PF; t++)
-        if (t < ntiles) issue_tile(t, t);
-    for (int t = 0; t < ntiles; t++) {
-        const int newer = min(PF - 1, ntiles - 1 - t);  // tiles issued after t
-        if constexpr (PF >= 3) {
-            if (newer >= 2) wait_vm<2 * IPW>();
-            else if (newer == 1) wait_vm<IPW>();
-            else wait_vm<0>();
-        } else {
-            if (newer >= 1) wait_vm<IPW>();
-            else wait_vm<0>();
+    const bool active = __builtin_amdgcn_readfirstlane(rg) * 32 < M;
+    const int ntiles = t1 - t0;
+    for (int c0 = 0; c0 < ntiles; c0 += chunk_tiles) {
+        const int c1 = min(ntiles, c0 + chunk_tiles);
+        // (the ring is idle here: every earlier tile has been multiplied or is about to be by
+        // waves that read no page id)
+        const int tb0 = p_begin + c0 * kTile;
+        slot0 = tb0 >> a.log2P;
+        const int nslots = ((min(p_end, p_begin + c1 * kTile) - 1) >> a.log2P) - slot0 + 1;
+        if (c0 > 0) pg0 = tid < nslots && slot0 + tid < a.maxp ? pt[slot0 + tid] : -1;
+        if (tid < nslots) lds.pid[tid] = (pg0 >= 0 && pg0 < a.num_pages) ? pg0 : -1;
+        for (int e = tid + NW * 64; e < nslots; e += NW * 64) {
+            const int pslot = slot0 + e;
+            const int pg = pslot < a.maxp ? pt[pslot] : -1;
+            lds.pid[e] = (pg >= 0 && pg < a.num_pages) ? pg : -1;
         }
-        // the last tile may reach past the split end: the lanes that copied those V rows
-        // (foreign data, possibly non-finite) zero them, so P = 0 there contributes exactly 0
-        if (t == ntiles - 1 && tok_begin + (t + 1) * kTile > tok_end && my_tensor == 1) {
-            const int tb = tok_begin + t * kTile;
-            char* vbuf = (char*)&lds.kv[0][0][0] + (t % NBUF) * 2 * LdsRing<HD, NBUF>::kTileBytes;
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // (as above: no load may be pending when the ring starts)
+        __syncthreads();                     // page ids visible, the previous chunk's tiles read
 #pragma unroll
-            for (int k = 0; k < IPW; k++)
-                if (tb + tk[k] >= tok_end) *(u16x8*)(vbuf + ldsoff[k] + 16 * lane) = u16x8{};
-        }
-        __syncthreads();
-        if (t + PF < ntiles) issue_tile(t + PF, (t + PF) % NBUF);
-        compute_tile(t % NBUF, tok_begin + t * kTile);
+        for (int t = 0; t < PF; t++)
+            if (c0 + t < c1) {
+                find_pages(c0 + t);
+                issue_tile(c0 + t);
+            }
+        find_pages(c0 + PF);
+        // Tile t: wait for its DMA (and only its), barrier (tile t visible to all waves; the
+        // buffer that the next issue fills no longer read), issue tile t + PF, look the pages of
+        // tile t + PF + 1 up, multiply. Waves without query rows only move data. (Both sides of
+        // that wave-uniform branch run the same number of barriers.) The last PF tiles have
+        // fewer loads behind them and, at the end of the context, a tail.
+        int buf = c0 % NBUF;
+        auto run = [&](auto with_rows) {
+            int t = c0;
+            for (; t + PF < c1; t++) {
+                wait_vm<(PF - 1) * IPW>();
+                __syncthreads();
+                issue_tile(t + PF);
+                find_pages(t + PF + 1);
+                if constexpr (decltype(with_rows)::value) compute_tile(lds.k[buf], lds.v[buf], p_begin + t * kTile);
+                buf = buf + 1 == NBUF ? 0 : buf + 1;
+            }
+            for (; t < c1; t++) {
+                wait_tiles<PF - 1, IPW>(c1 - 1 - t);
+                // the last tile may reach past the end: the lanes that copied those V rows (foreign
+                // data, possibly non-finite) zero them, so P = 0 there contributes exactly 0
+                if (t == ntiles - 1 && p_begin + (t + 1) * kTile > p_end && my_tensor == 1) {
+                    const int tb = p_begin + t * kTile;
+#pragma unroll
+                    for (int k = 0; k < IPW; k++)
+                        if (tb + tk[k] >= p_end) *(u16x8*)((char*)lds.v[buf] + ldsoff[k] + 16 * lane) = u16x8{};
+                }
+                __syncthreads();
+                if constexpr (decltype(with_rows)::value) compute_tile(lds.k[buf], lds.v[buf], p_begin + t * kTile);
+                buf = buf + 1 == NBUF ? 0 : buf + 1;
+            }
+        };
+        if (active) run(std::true_type{});
+        else run(std::false_type{});
     }
 
-    // HALVES == 2: merge the token halves of each row group. The odd wave parks O in the
-    // ring and (m, l) in the page-id area (both free now), the even wave combines and
-    // writes. Both waves hold the same (row, dim) elements in the same lanes and registers.
+    // HALVES == 2: the two waves of a row group merge their token halves. Both hold the same
+    // (row, dim) elements in the same lanes and registers; each parks the d-tiles the other
+    // one finishes in the ring (free now), and (m, l) in the page-id area, then combines and
+    // writes its own half of the d-tiles.
     float l_tot = l_run + __shfl_xor(l_run, 32, 64);
-    const bool grp_ok = rg * 32 < M;
+    constexpr int DO = HALVES == 2 ? DT / 2 : DT;  // d-tiles this wave writes, from d-tile th*DO
+    f32x16 of[DO];
     if constexpr (HALVES == 2) {
-        static_assert((NW / 2) * 64 * 16 * DT * sizeof(float) <= sizeof(lds.kv), "park O");
-        static_assert((NW / 2) * 96 * sizeof(float) <= sizeof(lds.pid), "park m, l");
+        static_assert(NW * 64 * 16 * DO * sizeof(float) <= sizeof(lds.k) + sizeof(lds.v), "park O");
+        static_assert(NW * 128 * sizeof(float) <= sizeof(lds.pid), "park m, l");
         __syncthreads();
-        float* park = (float*)&lds.kv[0][0][0] + (size_t)rg * (64 * 16 * DT);
-        float* park_ml = (float*)&lds.pid[0] + rg * 96;
-        if (grp_ok && th == 1) {
+        f32x4* park = (f32x4*)&lds.k[0][0] + lane;
+        float* park_ml = (float*)&lds.pid[0] + lane;
+        const bool odd = __builtin_amdgcn_readfirstlane(th);
+        auto put = [&](int from) {
 #pragma unroll
-            for (int t = 0; t < DT; t++)
+            for (int t = 0; t < DO; t++)
 #pragma unroll
-                for (int e = 0; e < 16; e++) park[(t * 16 + e) * 64 + lane] = o[t][e];
-            park_ml[lane] = m_run;
-            if (lane < 32) park_ml[64 + lane] = l_tot;  // rows in lanes 0..31
+                for (int g = 0; g < 4; g++)
+                    park[((w * DO + t) * 4 + g) * 64] = {o[from + t][4 * g], o[from + t][4 * g + 1], o[from + t][4 * g + 2],
+                                                         o[from + t][4 * g + 3]};
+        };
+        if (active) {
+            if (odd) put(0);
+            else put(DO);
+            park_ml[w * 128] = m_run;
+            park_ml[w * 128 + 64] = l_tot;
         }
         __syncthreads();
-        if (!grp_ok || th == 1 || !row_ok) return;
-        const float m2 = park_ml[lane];
-        const float l2 = park_ml[64 + (lane & 31)];
+        if (!active || !row_ok) return;
+        const int ow = w ^ 1;
+        const float m2 = park_ml[ow * 128], l2 = park_ml[ow * 128 + 64];
         const float mm = fmaxf(m_run, m2);
         const float a1 = __builtin_amdgcn_exp2f(m_run - mm), a2 = __builtin_amdgcn_exp2f(m2 - mm);
+        auto get = [&](int from) {
 #pragma unroll
-        for (int t = 0; t < DT; t++)
+            for (int t = 0; t < DO; t++)
 #pragma unroll
-            for (int e = 0; e < 16; e++) o[t][e] = o[t][e] * a1 + park[(t * 16 + e) * 64 + lane] * a2;
+                for (int g = 0; g < 4; g++) {
+                    const f32x4 v = park[((ow * DO + t) * 4 + g) * 64];
+#pragma unroll
+                    for (int e = 0; e < 4; e++) of[t][4 * g + e] = o[from + t][4 * g + e] * a1 + v[e] * a2;
+                }
+        };
+        if (odd) get(DO);
+        else get(0);
         l_tot = l_tot * a1 + l2 * a2;
         m_run = mm;
     } else {
-        if (!grp_ok || !row_ok) return;
+        if (!active || !row_ok) return;
+#pragma unroll
+        for (int t = 0; t < DO; t++) of[t] = o[t];
     }
     const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
     const float lse2 = l_tot > 0.0f ? m_run + __log2f(l_tot) : -INFINITY;
     const size_t orow = (size_t)(q0 + jq) * a.Hq + head;
-    if (nsplit == 1) {
-        uint16_t* op = (uint16_t*)a.out + orow * HD;
+    const int d0 = (HALVES == 2 ? th * DO * 32 : 0) + 4 * half;
+    if (t1 - t0 == nt) {
+        uint16_t* op = (uint16_t*)a.out + orow * HD + d0;
 #pragma unroll
-        for (int t = 0; t < DT; t++)
+        for (int t = 0; t < DO; t++)
 #pragma unroll
-            for (int g2 = 0; g2 < 4; g2++) {
-                const int dd = t * 32 + 8 * g2 + 4 * half;
-                uint64_t pk = 0;
+            for (int g = 0; g < 4; g++) {
+                bf16x4 v;
 #pragma unroll
-                for (int e = 0; e < 4; e++) pk |= (uint64_t)f2bf(o[t][4 * g2 + e] * inv) << (16 * e);
-                *(uint64_t*)(op + dd) = pk;
+                for (int e = 0; e < 4; e++) v[e] = (__bf16)(of[t][4 * g + e] * inv);
+                *(bf16x4*)(op + t * 32 + 8 * g) = v;
             }
-        if (a.lse && half == 0) a.lse[orow] = lse2 * kLn2;
+        if (a.lse && half == 0 && th == 0) a.lse[orow] = lse2 * kLn2;
     } else {
-        float* pp = a.part_o + ((size_t)s * a.total_q * a.Hq + orow) * HD;
+        const size_t prow = (size_t)slot * a.slot_rows + r;
+        float* pp = a.part_o + prow * HD + d0;
 #pragma unroll
-        for (int t = 0; t < DT; t++)
+        for (int t = 0; t < DO; t++)
 #pragma unroll
-            for (int g2 = 0; g2 < 4; g2++) {
-                const int dd = t * 32 + 8 * g2 + 4 * half;
-                f32x4 v = {o[t][4 * g2] * inv, o[t][4 * g2 + 1] * inv, o[t][4 * g2 + 2] * inv, o[t][4 * g2 + 3] * inv};
-                *(f32x4*)(pp + dd) = v;
+            for (int g = 0; g < 4; g++) {
+                f32x4 v;
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[e] = of[t][4 * g + e] * inv;
+                *(f32x4*)(pp + t * 32 + 8 * g) = v;
             }
-        if (half == 0) a.part_lse[(size_t)s * a.total_q * a.Hq + orow] = lse2;
+        if (half == 0 && th == 0) a.part_lse[prow] = lse2;
     }
 }
 
-// Work list of the persistent kernel (attn_plan.h), built by one workgroup.
-__global__ __launch_bounds__(1024) void attn_plan_kernel(AttnArgs a, int32_t* groups, int32_t* ctr) {
-    __shared__ int cursor[kPlanBuckets];
-    __shared__ int wsum[1024 / 64];
-    AttnPlanArgs pa{a.R, a.block, a.total_q, a.max_kv_len, a.split, a.Hkv, a.nrb, groups, ctr};
+// The plan (attn_plan.h), built by one workgroup.
+__global__ __launch_bounds__(1024) void attn_plan_kernel(RangeArgs a, AttnPlanArgs pa) {
+    __shared__ uint64_t pre[kPlanLdsReqs + 1];
+    __shared__ uint64_t wsum[1024 / 64];
     build_attn_plan<1024>(pa, [&](int i, int& q0, int& k_i, int& kv) {
         q0 = a.qo[i];
         k_i = a.qo[i + 1] - q0;
         kv = a.kv_lens[i];
-    }, cursor, wsum);
+    }, a.R <= kPlanLdsReqs ? pre : pa.pre, wsum);
 }
 
-template <int HD, int NW, int NBUF, bool ONEPAGE, bool WIDE>
-__global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(AttnArgs a, const int32_t* __restrict__ groups,
+// Persistent kernel: a workgroup takes the item of its own index, then claims further ones
+// from a counter when the plan has more items than the grid has workgroups.
+template <int HD, int NW, int NBUF, PageMode PM, bool WIDE>
+__global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, const AttnRange* __restrict__ recs,
                                                                int32_t* __restrict__ ctr) {
     __shared__ __attribute__((aligned(16))) LdsRing<HD, NBUF> lds;
     __shared__ int s_item;
-    // A work list that was never built (a run on a workspace without a plan) holds arbitrary
-    // values: its length is capped by the longest possible list, a negative claim ends the
-    // loop and items naming a request or split that does not exist are skipped, so every
-    // access stays in bounds (the results are then unspecified).
-    const int nitems = min(ctr[0], a.max_items);
-    const int per_group = a.Hkv * a.nrb;
+    // A plan that was never built (a run on a workspace without one) holds arbitrary values:
+    // the number of ranges is capped by what the workspace holds, a claim outside it ends the
+    // loop, and a cut that names no request, unit or tile is skipped, so every access stays in
+    // bounds and every loop ends (the results are then unspecified).
+    const int n = min(ctr[0], a.ranges) * a.Hkv;  // (below 2^31: checked on the host)
+    constexpr int RB = WIDE ? NW * 32 : NW * 16;
+    int item = blockIdx.x, claim = 0;
     for (;;) {
-        if (threadIdx.x == 0) s_item = atomicAdd(&ctr[1], 1);
-        __syncthreads();
-        const int item = s_item;
-        __syncthreads();
-        if (item < 0 || item >= nitems) break;
-        const uint32_t gv = (uint32_t)groups[item / per_group];  // request << 16 | split
-        const int within = item % per_group;
-        const int i = (int)(gv >> 16), h = within / a.nrb, s = (int)(gv & 0xFFFFu);
-        if (i >= a.R || s >= a.max_splits) continue;
-        const int row0 = (within % a.nrb) * (WIDE ? 2 * NW * 16 : NW * 16);
-        if (WIDE && a.G * (a.qo[i + 1] - a.qo[i]) - row0 > NW * 16)
-            attn_item<HD, NW, NBUF, ONEPAGE, 1>(a, lds, i, h, s, row0);
-        else
-            attn_item<HD, NW, NBUF, ONEPAGE, 2>(a, lds, i, h, s, row0);
+        // (opaque to the compiler, so that the claim stays at the head of the loop, in one
+        // loop with its barriers)
+        asm volatile("" : "+s"(claim));
+        if (claim) {
+            if (threadIdx.x == 0) s_item = (int)gridDim.x + atomicAdd(&ctr[1], 1);
+            __syncthreads();
+            item = s_item;
+            __syncthreads();
+        }
+        if (item < 0 || item >= (n <= (int)gridDim.x ? (n + 7) / 8 * 8 : n)) break;
+        // Workgroups go to the 8 XCDs round-robin: each XCD takes a contiguous part of the items,
+        // so that the heads of a range, whose K/V blocks are neighbours in every page, run on one
+        // XCD and share its address translations.
+        const int per_xcd = (n + 7) / 8;
+        const int seq = n <= (int)gridDim.x ? (item % 8) * per_xcd + item / 8 : item;
+        const int rng = seq / a.Hkv, h = seq % a.Hkv;
+        if (seq >= n) return;
+        const AttnRange r0 = recs[rng], r1 = recs[rng + 1];
+        int rb = r0.block, t = r0.tile;
+        for (int i = max(r0.req, 0); i <= r1.req && i < a.R; i++, rb = 0, t = 0) {
+            int q0 = r0.q0, k_i = r0.k, kv_len = r0.kv;
+            if (i != r0.req) {
+                q0 = a.qo[i];
+                k_i = a.qo[i + 1] - q0;
+                kv_len = a.kv_lens[i];
+            }
+            kv_len = min(kv_len, a.max_kv_len);
+            const int nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv_len);
+            if (nt == 0) continue;
+            const int rb_end = i == r1.req ? min(r1.block, a.nrb - 1) : a.nrb - 1;  // (the last unit, cut or whole)
+            for (rb = max(rb, 0); rb <= rb_end; rb++, t = 0) {
+                const int row0 = rb * RB;
+                const int t0 = max(t, 0), t1 = i == r1.req && rb == r1.block ? min(r1.tile, nt) : nt;
+                if (t0 >= t1 || a.G * k_i <= row0) continue;
+                const int slot = 2 * (rng * a.Hkv + h) + (t0 == 0);
+                if (WIDE && a.G * k_i - row0 > NW * 16)
+                    attn_item<HD, NW, NBUF, PM, 1>(a, lds, i, h, row0, q0, k_i, kv_len, t0, t1, nt, slot);
+                else
+                    attn_item<HD, NW, NBUF, PM, 2>(a, lds, i, h, row0, q0, k_i, kv_len, t0, t1, nt, slot);
+                __syncthreads();  // the LDS of this piece is free
+            }
+        }
+        if (n <= (int)gridDim.x) return;
+        claim = 1;
     }
     // the last workgroup to finish leaves the counters as the plan left them, so the
     // next call on the same plan (another layer of the round) starts clean: every
     // workgroup has made its last claim before it counts itself here
-    if (threadIdx.x == 0 && atomicAdd(&ctr[2], 1) == (int)gridDim.x - 1) {
+    if (n > (int)gridDim.x && threadIdx.x == 0 && atomicAdd(&ctr[2], 1) == (int)gridDim.x - 1) {
         ctr[1] = 0;
         ctr[2] = 0;
     }
 }
 
-
-// merge split partials: grid (row chunk, kv-head, request), one thread per (query row of
-// the group, 4-dim slice); every split's lse and partial are loaded before any math (one
-// round of loads for up to 8 splits). Requests with a single split were written
-// directly by the main kernel and exit here.
+// merge of the cut units' partials: grid (row chunk, kv-head, cut). The workgroups of the
+// first cut inside a unit merge its pieces: the one that starts it (the range before the cut)
+// and one per cut. One thread per (query row, 4-dim slice); up to 8 pieces' lse and partials
+// are loaded before any math.
 template <int HD, bool BF16OUT>
-__global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
+__global__ __launch_bounds__(256) void attn_merge_kernel(RangeArgs a, const AttnRange* __restrict__ recs,
+                                                         const int32_t* __restrict__ ctr, int rb_rows, int c0) {
     constexpr int SL = HD / 4;  // 4-dim slices per row
-    const int h = blockIdx.y, i = blockIdx.z;
-    const int q0 = a.qo[i], k_i = a.qo[i + 1] - q0;
-    int kv_len = a.kv_lens[i];
-    if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
-    if (k_i <= 0 || k_i > a.block || kv_len - k_i < 0 || q0 < 0 || q0 + k_i > a.total_q) return;
-    const int nsplit = (kv_len + a.split - 1) / a.split;
-    if (nsplit <= 1) return;
+    // one round of loads: the number of ranges, this cut, the one before and the 62 after
+    const int c = c0 + blockIdx.z + 1, h = blockIdx.y, lane = threadIdx.x & 63;
+    const int n = min(ctr[0], a.ranges);
+    const AttnRange mine = recs[min(c - 1 + lane, a.ranges)];
+    if (c >= n) return;
+    auto at = [&](int v, int l) { return __builtin_amdgcn_readlane(v, l); };
+    const int i = at(mine.req, 1), block = at(mine.block, 1);
+    if (at(mine.tile, 1) <= 0 || i < 0 || i >= a.R || block < 0 || block >= a.nrb) return;
+    if (at(mine.req, 0) == i && at(mine.block, 0) == block && at(mine.tile, 0) > 0) return;  // not the unit's first cut
+    const int q0 = at(mine.q0, 1), k_i = at(mine.k, 1);
+    // the cuts of this unit follow each other
+    uint64_t m = ~(__ballot(mine.req == i && mine.block == block && c - 1 + lane < n) | 1);
+    int last = c - 1 + (m ? __builtin_ctzll(m) : 64) - 1;
+    for (int b = c + 63; m == 0 && b < n; b += 64) {
+        const AttnRange rn = recs[min(b + lane, a.ranges)];
+        m = ~__ballot(rn.req == i && rn.block == block && b + lane < n);
+        last += m ? __builtin_ctzll(m) : 64;
+    }
+    if (k_i < 1 || k_i > a.block || q0 < 0 || q0 + k_i > a.total_q) return;  // (a plan of other inputs)
+    const int row0 = block * rb_rows;
+    const int M = min(a.G * k_i - row0, rb_rows);
     const int u = blockIdx.x * 256 + threadIdx.x;
-    if (u >= a.G * k_i * SL) return;
+    if (u >= M * SL) return;
     const int r = u / SL, sl = u % SL;
-    const size_t orow = (size_t)(q0 + r / a.G) * a.Hq + h * a.G + r % a.G;
-    const size_t sstride = (size_t)a.total_q * a.Hq;
+    const int rr = row0 + r;
+    const size_t orow = (size_t)(q0 + rr / a.G) * a.Hq + h * a.G + rr % a.G;
     float mx = -INFINITY, wsum = 0.0f;
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < nsplit; s0 += 8) {
+    for (int s0 = c - 1; s0 <= last; s0 += 8) {
         float lw[8];
         f32x4 v[8];
 #pragma unroll
         for (int k = 0; k < 8; k++) {
-            const bool ok = s0 + k < nsplit;
-            lw[k] = ok ? a.part_lse[(s0 + k) * sstride + orow] : -INFINITY;
-            v[k] = ok ? *(const f32x4*)(a.part_o + ((s0 + k) * sstride + orow) * HD + sl * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
+            const int s = s0 + k;
+            const size_t prow = (2 * ((size_t)s * a.Hkv + h) + (s == c - 1)) * a.slot_rows + r;
+            lw[k] = s <= last ? a.part_lse[prow] : -INFINITY;
+            v[k] = s <= last ? *(const f32x4*)(a.part_o + prow * HD + sl * 4) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
         float bm = mx;
 #pragma unroll
@@ -699,7 +760,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(AttnArgs a) {
 // ---------------------------------------------------------------------------------
 // fp32 vector kernel: one workgroup of four waves per (query row, head); HD <= 256, HD % 4 == 0
 // ---------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void attn_f32_kernel(AttnArgs a, int HD) {
+__global__ __launch_bounds__(256) void attn_f32_kernel(RangeArgs a, int HD) {
     // one workgroup per (row, head); wave wv takes the 64-key tiles wv, wv + 4, ... and the
     // four waves' softmax states are merged at the end
     __shared__ float s_o[4][4][64];
@@ -830,12 +891,26 @@ int ilog2(int x) {
 
 }  // namespace
 
+AttnPlanArgs attn_plan_args(const sv_attn_desc& d, const AttnPlan& p, void* ws) {
+    char* w = (char*)ws;
+    return AttnPlanArgs{d.num_reqs, d.block, d.total_q_max, d.max_kv_len, d.num_q_heads / d.num_kv_heads,
+                        p.row_blocks, (p.waves / p.halves) * 32, p.ranges,
+                        d.kv_split > 0 ? p.kv_split / kAttnTile : 0,
+                        d.num_kv_heads, (AttnRange*)(w + p.off_groups),
+                        (uint64_t*)(w + p.off_pre), (int32_t*)(w + p.off_ctr)};
+}
+
+AttnListArgs attn_list_args(const sv_attn_desc& d, const AttnPlan& p, void* ws) {
+    char* w = (char*)ws;
+    return AttnListArgs{d.num_reqs, d.block, d.total_q_max, d.max_kv_len, p.kv_split, d.num_kv_heads, p.row_blocks,
+                        (int32_t*)(w + p.off_groups), (int32_t*)(w + p.off_ctr)};
+}
 
 hipError_t launch_attn(const sv_attn_desc& d, const AttnPlan& plan, const void* q,
                        const void* k_cache, const void* v_cache, const int32_t* page_table,
                        const int32_t* qo_indptr, const int32_t* kv_lens, void* out, float* lse,
                        void* ws, hipStream_t stream, int phases) {
-    AttnArgs a{};
+    RangeArgs a{};
     a.q = q;
     a.kc = k_cache;
     a.vc = v_cache;
@@ -856,12 +931,12 @@ hipError_t launch_attn(const sv_attn_desc& d, const AttnPlan& plan, const void* 
     a.maxp = d.max_pages_per_req;
     a.num_pages = d.num_pages;
     a.max_kv_len = d.max_kv_len;
+    a.ranges = plan.ranges;
+    a.slot_rows = plan.slot_rows;
     a.split = plan.kv_split;
     a.max_splits = plan.max_splits;
-    {
-        const long long mi = (long long)d.num_reqs * plan.max_splits * d.num_kv_heads * plan.row_blocks;
-        a.max_items = mi > 0x7FFFFFFFLL ? 0x7FFFFFFF : (int)mi;
-    }
+    a.max_items = (int)std::min<long long>(
+        (long long)d.num_reqs * plan.max_splits * d.num_kv_heads * plan.row_blocks, 0x7FFFFFFF);
     a.scale = d.sm_scale > 0.0f ? d.sm_scale : 1.0f / sqrtf((float)d.head_dim);
     a.scale_log2 = a.scale * kLog2e;
 
@@ -887,40 +962,42 @@ hipError_t launch_attn(const sv_attn_desc& d, const AttnPlan& plan, const void* 
         cu_count[dev].store(ncu, std::memory_order_relaxed);
     }
     char* wsb = (char*)ws;
-    int32_t* groups = (int32_t*)(wsb + plan.off_groups);
+    if (plan.list)
+        return launch_attn_list(a, plan, d.head_dim, d.page_size, ncu, attn_list_args(d, plan, ws), stream,
+                                phases & kAttnPlan, phases & kAttnRun);
+    const AttnPlanArgs pa = attn_plan_args(d, plan, ws);
     int32_t* ctr = (int32_t*)(wsb + plan.off_ctr);
-    if (phases & kAttnPlan) hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, stream, a, groups, ctr);
+    if (phases & kAttnPlan) hipLaunchKernelGGL(attn_plan_kernel, dim3(1), dim3(1024), 0, stream, a, pa);
     if (!(phases & kAttnRun)) return hipGetLastError();
     const dim3 grid(ncu);
-#define SV_LAUNCH_ATTN(HDV, ONEP, HALV) \
-    hipLaunchKernelGGL((attn_bf16_kernel<HDV, 8, 4, ONEP, HALV == 1>), grid, dim3(8 * 64), 0, stream, a, groups, ctr)
-    const bool onepage = d.page_size >= kTile;
+#define SV_LAUNCH_ATTN(HDV, NB, PMODE, WIDE) \
+    hipLaunchKernelGGL((attn_bf16_kernel<HDV, 8, NB, PageMode::PMODE, WIDE>), grid, dim3(8 * 64), 0, stream, a, \
+                       pa.recs, ctr)
+#define SV_LAUNCH_PAGES(HDV, NB, WIDE) \
+    if (d.page_size >= kTile) SV_LAUNCH_ATTN(HDV, NB, kTile, WIDE); \
+    else if (d.page_size >= 512 / HDV) SV_LAUNCH_ATTN(HDV, NB, kSegment, WIDE); \
+    else SV_LAUNCH_ATTN(HDV, NB, kLane, WIDE)
     if (plan.halves == 2) {
-        if (d.head_dim == 128) {
-            if (onepage) SV_LAUNCH_ATTN(128, true, 2);
-            else SV_LAUNCH_ATTN(128, false, 2);
-        } else {
-            if (onepage) SV_LAUNCH_ATTN(64, true, 2);
-            else SV_LAUNCH_ATTN(64, false, 2);
-        }
+        if (d.head_dim == 128) { SV_LAUNCH_PAGES(128, 4, false); }
+        else { SV_LAUNCH_PAGES(64, 4, false); }
     } else {
-        if (d.head_dim == 128) {
-            if (onepage) SV_LAUNCH_ATTN(128, true, 1);
-            else SV_LAUNCH_ATTN(128, false, 1);
-        } else {
-            if (onepage) SV_LAUNCH_ATTN(64, true, 1);
-            else SV_LAUNCH_ATTN(64, false, 1);
-        }
+        if (d.head_dim == 128) { SV_LAUNCH_PAGES(128, 4, true); }
+        else { SV_LAUNCH_PAGES(64, 4, true); }
     }
+#undef SV_LAUNCH_PAGES
 #undef SV_LAUNCH_ATTN
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || plan.max_splits <= 1) return e;
-    const int rows_per_group = (d.num_q_heads / d.num_kv_heads) * d.block;
-    const dim3 mgrid((rows_per_group * (d.head_dim / 4) + 255) / 256, d.num_kv_heads, d.num_reqs);
-    if (d.head_dim == 128)
-        hipLaunchKernelGGL((attn_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, a);
-    else
-        hipLaunchKernelGGL((attn_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, a);
+    if (e != hipSuccess || plan.ranges <= 1) return e;
+    // (grids y and z are limited to 65535: more cuts than that come from tiny split sizes only;
+    // more heads are refused)
+    for (int c0 = 0; c0 < plan.ranges - 1; c0 += 65535) {
+        const dim3 mgrid((plan.slot_rows * (d.head_dim / 4) + 255) / 256, d.num_kv_heads,
+                         std::min(plan.ranges - 1 - c0, 65535));
+        if (d.head_dim == 128)
+            hipLaunchKernelGGL((attn_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows, c0);
+        else
+            hipLaunchKernelGGL((attn_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows, c0);
+    }
     return hipGetLastError();
 }
 

@@ -1,11 +1,16 @@
-// Work list of the persistent verify-attention kernel, built by one workgroup. Every
-// (request, split) group is bucketed by its tile count: full splits share the top bucket,
-// a request's shorter last split lands in the bucket of its own length. The buckets are
-// laid out in decreasing size (a counting sort), so the persistent workgroups take the
-// long items early and the short ones fill the tail. The order inside a bucket is
-// unspecified and does not affect any result: every item writes its own output rows or
-// partial slot. Used by the attention call's own plan kernel and by the round set-up
-// kernel (sv_prepare_round), so both build the same list.
+// Work plan of the persistent verify-attention kernel, built by one workgroup.
+//
+// Every kv-head has the same work, so the plan is made for one head. A unit is a (request, row
+// block), a run of 64-token tiles of the request's context; the units are laid end to end on a
+// line and the line is cut into ranges of equal cost. A work item is one range of one head, one
+// item per compute unit: the end of one unit, any number of whole units, the start of another.
+// A unit that a cut falls into leaves one fp32 partial result per piece, which the merge kernel
+// combines; an uncut unit is written directly. So the chip is filled evenly whatever the
+// lengths are, and at most one unit per cut needs a merge. The heads of a range are
+// neighbouring items, which run at the same time and read the same pages.
+// With a split size given by the caller the ranges are that many tokens long instead.
+// Used by the attention call's own plan kernel and by the round set-up kernel
+// (sv_prepare_round), so both build the same plan.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -13,105 +18,163 @@
 
 namespace sv {
 
-constexpr int kAttnTile = 64;         // KV tokens per tile of the attention kernel
-constexpr int kPlanBuckets = 1024;    // tile counts 1..1024; longer splits share the last
+constexpr int kAttnTile = 64;       // KV tokens per tile of the attention kernel
+constexpr int kPlanMinTiles = 6;    // no range of the automatic plan is shorter
+constexpr int kPlanGrid = 256;      // compute units
+constexpr int kPlanLdsReqs = 2048;  // the plan kernel keeps the costs of more requests in the workspace
+constexpr int kPlanSnapTiles = 2;   // a cut this close to a unit's end is moved onto it
+// Cost of a unit, in sixteenths of the time of one tile of a unit of at most 64 query rows
+// (bound by its K/V stream): its start and end (descriptors, page ids, queries, the first
+// tile's latency, the merge of the token halves: 6.3 us, 9.8 us above 64 rows) and its tiles.
+// Above 64 rows the tile's matrix and vector work shows (1.3 against 1.05 us), and above 128
+// rows (whole-tile waves) it bounds the tile (1.9 us).
+constexpr unsigned kCostStart = 100, kCostStart65 = 144, kCostTile = 16, kCostTile65 = 20, kCostWideTile = 32;
+// Workgroups on the odd XCDs end 3 to 4% later than those on the even ones with the same work
+// (attention over 188 MB to 6.4 GB, several cards), so their ranges are this many 1024ths
+// shorter and the others' longer.
+constexpr unsigned kOddXcd = 17;
 
-struct AttnPlanArgs {
-    int R, block, total_q, max_kv_len, split, Hkv, nrb;
-    int32_t* groups;  // [R * max_splits] request << 16 | split
-    int32_t* ctr;     // {work items, work counter, finished workgroups}
+// one cut of the line: the range starts at this tile of this unit. The request's packing and
+// key count go with it, which saves the readers a dependent load.
+struct __attribute__((aligned(16))) AttnRange {
+    int32_t req, block, tile, q0;
+    int32_t k, kv, pad0, pad1;
 };
 
-// splits of request i (0 when its packing is malformed) and the tile count of its last one
-__device__ inline int plan_splits(const AttnPlanArgs& a, int q0, int k_i, int kv_len, int& last_tiles) {
-    if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
-    last_tiles = 0;
-    if (!(k_i >= 1 && k_i <= a.block && kv_len - k_i >= 0 && q0 >= 0 && q0 + k_i <= a.total_q)) return 0;
-    const int ns = (kv_len + a.split - 1) / a.split;
-    last_tiles = (kv_len - (ns - 1) * a.split + kAttnTile - 1) / kAttnTile;
-    return ns;
+struct AttnPlanArgs {
+    int R, block, total_q, max_kv_len, G, nrb;
+    int rb_rows;       // query rows per row block
+    int ranges;        // most ranges per head the workspace holds
+    int range_tiles;   // tiles per range (a split size was given), or 0: ranges of equal cost
+    int heads;         // kv-heads
+    AttnRange* recs;   // [ranges + 1]
+    uint64_t* pre;     // [R + 1] cost before each request, used above kPlanLdsReqs requests
+    int32_t* ctr;      // {ranges per head, claim counter, finished workgroups}
+};
+
+// tiles of request i's context, 0 when its packing is malformed
+__device__ inline int plan_tiles(int block, int total_q, int max_kv_len, int q0, int k_i, int kv_len) {
+    if (kv_len > max_kv_len) kv_len = max_kv_len;
+    if (!(k_i >= 1 && k_i <= block && kv_len - k_i >= 0 && q0 >= 0 && q0 + k_i <= total_q)) return 0;
+    return (kv_len + kAttnTile - 1) / kAttnTile;
 }
 
-// NT threads of one workgroup (NT a multiple of 64 dividing kPlanBuckets); cursor:
-// kPlanBuckets ints of LDS, wsum: NT / 64 ints of LDS. req(i, q0, k_i, kv_len) gives
-// request i's packing and key count. Ends with a barrier-free store of the counters; the
-// caller's kernel end publishes the list.
+// cost per tile and of the start of a unit with M query rows
+__device__ inline unsigned plan_tile_cost(const AttnPlanArgs& a, int M) {
+    return a.range_tiles ? 1u : M > 128 ? kCostWideTile : M > 64 ? kCostTile65 : kCostTile;
+}
+__device__ inline unsigned plan_start_cost(const AttnPlanArgs& a, int M) {
+    return a.range_tiles ? 0u : M > 64 ? kCostStart65 : kCostStart;
+}
+__device__ inline unsigned plan_unit_cost(const AttnPlanArgs& a, int M, int nt) {
+    if (M <= 0 || nt <= 0) return 0;
+    return plan_start_cost(a, M) + (unsigned)nt * plan_tile_cost(a, M);
+}
+__device__ inline unsigned plan_head_cost(const AttnPlanArgs& a, int k_i, int nt) {
+    unsigned c = 0;
+    for (int rb = 0; rb < a.nrb; rb++) c += plan_unit_cost(a, a.G * k_i - rb * a.rb_rows, nt);
+    return c;
+}
+
+// NT threads of one workgroup. pre: R + 1 entries in LDS (or a.pre); wsum: NT / 64 entries of
+// LDS. req(i, q0, k_i, kv_len) gives request i's packing and key count. The caller's kernel
+// end publishes the plan.
 template <int NT, typename ReqFn>
-__device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, int* cursor, int* wsum) {
-    static_assert(NT % 64 == 0 && kPlanBuckets % NT == 0, "plan threads");
-    constexpr int BPT = kPlanBuckets / NT;  // buckets per thread in the scan
+__device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint64_t* pre, uint64_t* wsum) {
+    static_assert(NT % 64 == 0, "plan threads");
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const int full_tiles = a.split / kAttnTile;
-    auto bucket = [](int tiles) { return tiles < kPlanBuckets ? tiles - 1 : kPlanBuckets - 1; };
-    const int fb = bucket(full_tiles);
-    for (int k = tid; k < kPlanBuckets; k += NT) cursor[k] = 0;
-    __syncthreads();
-    // 1. histogram of group sizes (full splits summed per wave first: one shared bucket)
-    for (int base = 0; base < a.R; base += NT) {
-        const int i = base + tid;
-        int last = 0, ns = 0;
-        if (i < a.R) {
-            int q0, k_i, kv;
-            req(i, q0, k_i, kv);
-            ns = plan_splits(a, q0, k_i, kv, last);
-        }
-        int full = ns > 1 ? ns - 1 : 0;
-        for (int off = 32; off > 0; off >>= 1) full += __shfl_xor(full, off, 64);
-        if (lane == 0 && full) atomicAdd(&cursor[fb], full);
-        if (ns > 0) atomicAdd(&cursor[bucket(last)], 1);
+    auto head_cost = [&](int i, int& k_i, int& nt) {
+        int q0, kv;
+        req(i, q0, k_i, kv);
+        nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv);
+        return plan_head_cost(a, k_i, nt);
+    };
+    // 1. cost before each request: thread t takes requests t*per .. t*per + per - 1
+    const int per = (a.R + NT - 1) / NT;
+    uint64_t loc = 0;
+    for (int e = 0; e < per; e++) {
+        const int i = tid * per + e;
+        int k_i, nt;
+        if (i < a.R) loc += head_cost(i, k_i, nt);
     }
-    __syncthreads();
-    // 2. bucket starts in decreasing size: thread t scans positions t*BPT .. t*BPT+BPT-1 of
-    //    the descending bucket order (bucket kPlanBuckets-1-position)
-    int cnt[BPT];
-    int loc = 0;
-#pragma unroll
-    for (int e = 0; e < BPT; e++) {
-        cnt[e] = cursor[kPlanBuckets - 1 - (tid * BPT + e)];
-        loc += cnt[e];
-    }
-    int incl = loc;
+    uint64_t incl = loc;
     for (int off = 1; off < 64; off <<= 1) {
-        const int v = __shfl_up(incl, off, 64);
+        const uint64_t v = __shfl_up(incl, off, 64);
         if (lane >= off) incl += v;
     }
     if (lane == 63) wsum[w] = incl;
     __syncthreads();
-    int pre = 0;
-    for (int k = 0; k < w; k++) pre += wsum[k];
-    int pos = pre + incl - loc;
-#pragma unroll
-    for (int e = 0; e < BPT; e++) {
-        cursor[kPlanBuckets - 1 - (tid * BPT + e)] = pos;
-        pos += cnt[e];
+    uint64_t base = incl - loc, W = 0;
+    for (int k = 0; k < NT / 64; k++) {
+        if (k < w) base += wsum[k];
+        W += wsum[k];
     }
-    if (tid == NT - 1) {
-        a.ctr[0] = pos * a.Hkv * a.nrb;
+    for (int e = 0; e < per; e++) {
+        const int i = tid * per + e;
+        if (i > a.R) break;
+        pre[i] = base;
+        int k_i, nt;
+        if (i < a.R) base += head_cost(i, k_i, nt);
+    }
+    if (tid == 0) pre[a.R] = W;
+    __syncthreads();
+    // 2. the size of the ranges
+    const bool automatic = a.range_tiles == 0;
+    uint64_t step;
+    if (automatic) {
+        const uint64_t least = kCostStart + kPlanMinTiles * kCostTile;
+        const uint64_t up = W + (unsigned)a.ranges - 1;
+        step = up >> 32 ? up / (unsigned)a.ranges : (unsigned)up / (unsigned)a.ranges;
+        if (step < least) step = least;
+    } else {
+        step = (uint64_t)a.range_tiles;
+    }
+    const uint64_t upto = W + step - 1;
+    const uint64_t want = upto >> 32 || step >> 32 ? upto / step : (unsigned)upto / (unsigned)step;
+    const int n = want < (uint64_t)a.ranges ? (int)want : a.ranges;
+    // the items of a range share an XCD when its workgroups hold whole ranges (attn.hip)
+    const bool skewed = automatic && n % 8 == 0 && n * a.heads <= kPlanGrid;
+    // 3. the cuts: the request by binary search over the costs, then row block and tile
+    for (int r = tid; r <= n; r += NT) {
+        uint64_t at = (uint64_t)r * step;
+        if (skewed) {  // (per XCD the ranges' sizes sum to per * step on average over two XCDs)
+            const unsigned per = (unsigned)n / 8, x = (unsigned)r / per, k = (unsigned)r % per;
+            at += (x & 1 ? per - k : k) * (step * kOddXcd / 1024);
+        }
+        AttnRange rec{a.R, 0, 0, 0, 0, 0, 0, 0};
+        if (r < n && at < W) {
+            int lo = 0, hi = a.R - 1;  // the last request whose cost starts at or before `at`
+            while (lo < hi) {
+                const int mid = (lo + hi + 1) >> 1;
+                if (pre[mid] <= at) lo = mid;
+                else hi = mid - 1;
+            }
+            int q0, k_i, kv;
+            req(lo, q0, k_i, kv);
+            const int nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv);
+            unsigned x = (unsigned)(at - pre[lo]);
+            int rb = 0;
+            unsigned uc = plan_unit_cost(a, a.G * k_i, nt);
+            while (x >= uc && rb + 1 < a.nrb) {
+                x -= uc;
+                rb++;
+                uc = plan_unit_cost(a, a.G * k_i - rb * a.rb_rows, nt);
+            }
+            const unsigned start = plan_start_cost(a, a.G * k_i - rb * a.rb_rows);
+            int t = x > start ? (int)((x - start) / plan_tile_cost(a, a.G * k_i - rb * a.rb_rows)) : 0;
+            if (automatic && t <= kPlanSnapTiles) t = 0;
+            if (t >= nt || (automatic && nt - t <= kPlanSnapTiles && t > 0)) {
+                t = 0;
+                rb++;
+            }
+            rec = AttnRange{lo, rb, t, q0, k_i, kv, 0, 0};
+        }
+        a.recs[r] = rec;
+    }
+    if (tid == 0) {
+        a.ctr[0] = n;
         a.ctr[1] = 0;
         a.ctr[2] = 0;
-    }
-    __syncthreads();
-    // 3. place the groups (full splits: one atomic per wave, positions by a wave scan)
-    for (int base = 0; base < a.R; base += NT) {
-        const int i = base + tid;
-        int last = 0, ns = 0;
-        if (i < a.R) {
-            int q0, k_i, kv;
-            req(i, q0, k_i, kv);
-            ns = plan_splits(a, q0, k_i, kv, last);
-        }
-        const int full = ns > 1 ? ns - 1 : 0;
-        int fincl = full;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int v = __shfl_up(fincl, off, 64);
-            if (lane >= off) fincl += v;
-        }
-        int fbase = 0;
-        if (lane == 63 && fincl) fbase = atomicAdd(&cursor[fb], fincl);
-        fbase = __shfl(fbase, 63, 64);
-        const int p0 = fbase + fincl - full;
-        for (int t = 0; t < full; t++) a.groups[p0 + t] = (int32_t)(((uint32_t)i << 16) | (uint32_t)t);
-        if (ns > 0) a.groups[atomicAdd(&cursor[bucket(last)], 1)] = (int32_t)(((uint32_t)i << 16) | (uint32_t)(ns - 1));
     }
 }
 

@@ -7,6 +7,8 @@
 // registers; only strides of 64 threads or more go through LDS); the top K_j of every
 // candidate ratio are then prefixes of the sorted order, so one prefix sum gives every
 // utility, and the keep counts need no second selection.
+#include <type_traits>
+
 #include "attn_plan.h"
 #include "sv_internal.h"
 
@@ -31,6 +33,9 @@ struct BudgetArgs {
 // (sv_prepare_round): the dense verify batch of the kept prefixes (sv_pack_verify's
 // arithmetic) and, when `plan` is set, the verify-attention work plan over the key counts
 // the packing produced (attn_plan.h).
+// Plan: AttnPlanArgs (ranges) or AttnListArgs (work list), each in a kernel of its own: one that
+// held both took 0.4 us more (64 requests x 16 positions: 14.5 against 14.1 us).
+template <typename Plan>
 struct PrepArgs {
     const int32_t* block_tokens;  // [R, b]
     const int32_t* ctx;           // [R]
@@ -39,7 +44,7 @@ struct PrepArgs {
     int32_t* kv_lens;             // [R]
     int total_max;
     int plan;
-    AttnPlanArgs pa;
+    Plan pa;
 };
 
 __device__ inline float clamp_conf(float c) {
@@ -76,20 +81,20 @@ __device__ inline uint64_t shfl_up_u64(uint64_t v, int d) {
 // Bitonic stages with stride < KPT run in registers, < 64*KPT across lanes of a wave, the
 // rest through LDS (ping-pong buffers, one barrier per stage). Small rounds run on one
 // wave (NT = 64, at most 128 keys), where every stage stays in registers and shuffles
-// and the barriers are a single wave's. (At 256 keys the one-wave form's sort is still
-// faster, but its attention plan, 1024 buckets over 64 threads, costs more than that.)
-template <int NT, int KPT, bool PREP>
+// and the barriers are a single wave's.
+template <int NT, int KPT, bool PREP, typename Plan>
 __global__ __launch_bounds__(NT) void budget_kernel(BudgetArgs a, const float* __restrict__ conf,
                                                           int32_t* __restrict__ keep,
                                                           int32_t* __restrict__ qo_indptr,
                                                           int32_t* __restrict__ sel,
                                                           float* __restrict__ scores_out,
-                                                          uint64_t* __restrict__ util_out, PrepArgs pr) {
+                                                          uint64_t* __restrict__ util_out, PrepArgs<Plan> pr) {
     static_assert(NT == kThreads || (NT == kWave && KPT * NT <= kSmallMax), "budget workgroup");
     constexpr int NPAD = KPT * NT;
-    // requests: up to kMaxReqs (large rounds) or kSmallMax (one wave); with PREP the
-    // one-wave form keeps the attention plan's bucket cursors after them
-    constexpr int NCNT = NT == kThreads ? kMaxReqs : kSmallMax + kPlanBuckets;
+    // requests: up to kMaxReqs (large rounds) or kSmallMax (one wave); the one-wave form
+    // keeps a work list's bucket cursors after them
+    constexpr int NCNT =
+        NT == kThreads ? kMaxReqs : kSmallMax + (PREP && std::is_same_v<Plan, AttnListArgs> ? kPlanBuckets : 0);
     __shared__ uint64_t lds[2][NPAD];
     __shared__ int cnt[NCNT];
     __shared__ uint64_t wtot[NT / 64];
@@ -273,12 +278,17 @@ __global__ __launch_bounds__(NT) void budget_kernel(BudgetArgs a, const float* _
         if (!pr.plan) return;
         __syncthreads();
         // 8. the verify-attention work plan over those key counts
-        int* cursor = NT == kThreads ? qs + ((R + 1 + 63) & ~63) : cnt + kSmallMax;
-        build_attn_plan<NT>(pr.pa, [&](int i, int& q0, int& k_i, int& kv) {
+        // (ranges: the costs before each request go to the second key buffer: R <= NPAD, and the
+        // packing offsets fill at most half of the first)
+        auto req = [&](int i, int& q0, int& k_i, int& kv) {
             q0 = qs[i];
             k_i = qs[i + 1] - q0;
             kv = kvs[i];
-        }, cursor, scan_tmp);
+        };
+        if constexpr (std::is_same_v<Plan, AttnListArgs>)
+            build_attn_list<NT>(pr.pa, req, NT == kThreads ? qs + ((R + 1 + 63) & ~63) : cnt + kSmallMax, scan_tmp);
+        else
+            build_attn_plan<NT>(pr.pa, req, &lds[0][0] + (R + 2) / 2, wtot);
     }
 }
 
@@ -305,14 +315,14 @@ BudgetArgs budget_args(const sv_budget_desc& d) {
     return a;
 }
 
-template <bool PREP>
+template <bool PREP, typename Plan>
 hipError_t launch_budget_kernel(const sv_budget_desc& d, const float* conf, int32_t* keep, int32_t* qo_indptr,
-                                int32_t* sel, float* scores, uint64_t* utility, const PrepArgs& pr,
+                                int32_t* sel, float* scores, uint64_t* utility, const PrepArgs<Plan>& pr,
                                 hipStream_t stream) {
     const BudgetArgs a = budget_args(d);
     const int64_t N = (int64_t)d.num_reqs * d.block;
 #define SV_LAUNCH_BUDGET(T, KP) \
-    hipLaunchKernelGGL((budget_kernel<T, KP, PREP>), dim3(1), dim3(T), 0, stream, a, conf, keep, qo_indptr, sel, \
+    hipLaunchKernelGGL((budget_kernel<T, KP, PREP, Plan>), dim3(1), dim3(T), 0, stream, a, conf, keep, qo_indptr, sel, \
                        scores, utility, pr)
     if (N <= kSmallMax) {  // (R <= N)
         if (N <= kWave) SV_LAUNCH_BUDGET(kWave, 1);
@@ -334,28 +344,34 @@ hipError_t launch_budget_kernel(const sv_budget_desc& d, const float* conf, int3
 hipError_t launch_budget(const sv_budget_desc& d, const float* conf, int32_t* keep,
                          int32_t* qo_indptr, int32_t* sel, float* scores, uint64_t* utility,
                          hipStream_t stream) {
-    return launch_budget_kernel<false>(d, conf, keep, qo_indptr, sel, scores, utility, PrepArgs{}, stream);
+    return launch_budget_kernel<false>(d, conf, keep, qo_indptr, sel, scores, utility, PrepArgs<AttnPlanArgs>{}, stream);
 }
 
 hipError_t launch_prepare(const sv_budget_desc& d, const float* conf, int32_t* keep, int32_t* qo_indptr,
                           int32_t* sel, float* scores, uint64_t* utility, const int32_t* block_tokens,
                           const int32_t* ctx_lens, int32_t* tokens, int32_t* positions, int32_t* kv_lens,
                           int total_max, const sv_attn_desc* ad, void* attn_ws, hipStream_t stream) {
-    PrepArgs pr{};
-    pr.block_tokens = block_tokens;
-    pr.ctx = ctx_lens;
-    pr.tokens = tokens;
-    pr.positions = positions;
-    pr.kv_lens = kv_lens;
-    pr.total_max = total_max;
-    if (ad && ad->dtype == SV_BF16) {  // the fp32 path has no work plan
-        const AttnPlan p = plan_attn(*ad);
+    auto launch = [&](auto pr) {
+        pr.block_tokens = block_tokens;
+        pr.ctx = ctx_lens;
+        pr.tokens = tokens;
+        pr.positions = positions;
+        pr.kv_lens = kv_lens;
+        pr.total_max = total_max;
+        return launch_budget_kernel<true>(d, conf, keep, qo_indptr, sel, scores, utility, pr, stream);
+    };
+    if (!ad || ad->dtype != SV_BF16) return launch(PrepArgs<AttnPlanArgs>{});  // the fp32 path has no work plan
+    const AttnPlan p = plan_attn(*ad);
+    if (p.list) {
+        PrepArgs<AttnListArgs> pr{};
         pr.plan = 1;
-        pr.pa = AttnPlanArgs{ad->num_reqs, ad->block, ad->total_q_max, ad->max_kv_len, p.kv_split, ad->num_kv_heads,
-                             p.row_blocks, (int32_t*)((char*)attn_ws + p.off_groups),
-                             (int32_t*)((char*)attn_ws + p.off_ctr)};
+        pr.pa = attn_list_args(*ad, p, attn_ws);
+        return launch(pr);
     }
-    return launch_budget_kernel<true>(d, conf, keep, qo_indptr, sel, scores, utility, pr, stream);
+    PrepArgs<AttnPlanArgs> pr{};
+    pr.plan = 1;
+    pr.pa = attn_plan_args(*ad, p, attn_ws);
+    return launch(pr);
 }
 
 }  // namespace sv

@@ -4,6 +4,7 @@
 // its own with g++ under AddressSanitizer and UndefinedBehaviorSanitizer.
 #include "sv_host.h"
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -212,38 +213,67 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
         p.max_splits = 1;
         return p;
     }
-    int split = d.kv_split;
-    if (split <= 0) {
-        // About 8 work items per compute unit if every request had the longest context:
-        // R * Hkv * max_kv_len head-tokens over 256 CUs, divided by 8, at least 2048
-        // tokens. Measured over split sizes 1024..24576, this picks the best or nearly the
-        // best one on c64_b16 (8192), long_c32 (8192), the C5 c64 sweep (16384) and the
-        // small rounds (2048 at 4..16 requests): fewer, longer items save per-item
-        // prologues and merge work until the last items to finish start to dominate, and
-        // below 2048 tokens the per-item costs outweigh the extra parallelism. The host
-        // does not see the lengths themselves (they live on the device), so the bound
-        // uses max_kv_len.
-        long long want = (long long)d.num_reqs * d.num_kv_heads * d.max_kv_len / (256 * 8);
-        if (want < 2048) want = 2048;
-        split = (int)(((want + 63) / 64) * 64);
-    }
-    if (split > d.max_kv_len) split = ((d.max_kv_len + 63) / 64) * 64;
-    // a split's page ids are staged in LDS: at most 1024 pages per split (a split of
-    // n tokens starting on a 64-token boundary touches at most n / P + 2 pages)
-    const long long max_split = 1022LL * d.page_size;
-    if (split > max_split) split = (int)(max_split / 64 * 64);
-    if (split < 64) split = 64;
-    p.kv_split = split;
-    p.max_splits = (d.max_kv_len + split - 1) / split;
-    if (p.max_splits < 1) p.max_splits = 1;
-    if (p.max_splits > 1) {
-        p.part_o_bytes = (size_t)p.max_splits * d.total_q_max * d.num_q_heads * d.head_dim * sizeof(float);
-        p.part_lse_bytes = (size_t)p.max_splits * d.total_q_max * d.num_q_heads * sizeof(float);
-    }
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    // Two units per compute unit and more: a work list (attn_list.hip, with what either side
+    // measured).
+    if ((long long)d.num_reqs * d.num_kv_heads * p.row_blocks >= 2 * kAttnItems) {
+        p.list = true;
+        int split = d.kv_split;
+        if (split <= 0) {
+            // About 8 work items per compute unit if every request had the longest context:
+            // R * Hkv * max_kv_len head-tokens over 256 CUs, divided by 8, at least 2048
+            // tokens. Measured over split sizes 1024..24576, this picks the best or nearly the
+            // best one on 64 requests of up to 32768 tokens (8192) and of up to 65536 (16384):
+            // fewer, longer items save per-item prologues and merge work until the last items to
+            // finish start to dominate, and below 2048 tokens the per-item costs outweigh the
+            // extra parallelism. The host does not see the lengths themselves (they live on the
+            // device), so the bound uses max_kv_len.
+            long long want = (long long)d.num_reqs * d.num_kv_heads * d.max_kv_len / (256 * 8);
+            if (want < 2048) want = 2048;
+            split = (int)(((want + 63) / 64) * 64);
+        }
+        if (split > d.max_kv_len) split = ((d.max_kv_len + 63) / 64) * 64;
+        // a split's page ids are staged in LDS: at most 1024 pages per split (a split of
+        // n tokens starting on a 64-token boundary touches at most n / P + 2 pages)
+        const long long max_split = 1022LL * d.page_size;
+        if (split > max_split) split = (int)(max_split / 64 * 64);
+        if (split < 64) split = 64;
+        p.kv_split = split;
+        p.max_splits = (d.max_kv_len + split - 1) / split;
+        if (p.max_splits < 1) p.max_splits = 1;
+        if (p.max_splits > 1) {
+            p.part_o_bytes = (size_t)p.max_splits * d.total_q_max * d.num_q_heads * d.head_dim * sizeof(float);
+            p.part_lse_bytes = (size_t)p.max_splits * d.total_q_max * d.num_q_heads * sizeof(float);
+        }
+        p.off_groups = al(p.part_o_bytes + p.part_lse_bytes);
+        p.off_ctr = al(p.off_groups + (size_t)d.num_reqs * p.max_splits * sizeof(int32_t));
+        p.ws_bytes = p.off_ctr + 3 * sizeof(int32_t);  // work items, work counter, finished workgroups
+        return p;
+    }
+    // The plan (attn_plan.h) cuts each kv-head's work into ranges: as many as give all heads
+    // together one item per compute unit (no more than the longest contexts hold tiles) or,
+    // when the caller gives a split size, ranges of that many tokens. Head counts that would
+    // leave over a tenth of the compute units without an item get about four items per unit.
+    const int hkv = d.num_kv_heads;
+    int per_head = hkv <= kAttnItems ? kAttnItems / hkv : 0;
+    if (per_head * hkv * 10 < kAttnItems * 9) per_head = (4 * kAttnItems + hkv - 1) / hkv;
+    const long long whole = ((long long)d.max_kv_len + 63) / 64 * 64;
+    p.kv_split = d.kv_split > 0 && d.kv_split < whole ? d.kv_split : (int)whole;
+    p.max_splits = (d.max_kv_len + p.kv_split - 1) / p.kv_split;
+    const long long units = (long long)d.num_reqs * p.row_blocks;
+    const long long most = d.kv_split > 0 ? units * p.max_splits : std::min<long long>(per_head, units * (whole / 64));
+    p.ranges = (int)std::min<long long>(most, 0x7FFFFFF0LL / d.num_kv_heads);  // (items fit an int)
+    p.slot_rows = std::min(maxM, rows);
+    if (p.ranges > 1) {  // two partial results per item: a unit that continues into it and one that starts there
+        const size_t slots = 2 * (size_t)p.ranges * d.num_kv_heads * p.slot_rows;
+        p.part_o_bytes = slots * d.head_dim * sizeof(float);
+        p.part_lse_bytes = slots * sizeof(float);
+    }
     p.off_groups = al(p.part_o_bytes + p.part_lse_bytes);
-    p.off_ctr = al(p.off_groups + (size_t)d.num_reqs * p.max_splits * sizeof(int32_t));
-    p.ws_bytes = p.off_ctr + 3 * sizeof(int32_t);  // work items, work counter, finished workgroups
+    p.off_pre = al(p.off_groups + ((size_t)p.ranges + 1) * 32);
+    p.off_ctr = al(std::max(p.off_pre + ((size_t)d.num_reqs + 1) * 8,
+                            p.off_groups + (size_t)d.num_reqs * p.max_splits * sizeof(int32_t)));
+    p.ws_bytes = p.off_ctr + 3 * sizeof(int32_t);
     return p;
 }
 

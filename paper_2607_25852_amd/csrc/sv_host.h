@@ -26,16 +26,21 @@ struct ReqPlan {
 }  // namespace acc
 
 // ---- workspace layouts --------------------------------------------------------------
+constexpr int kAttnItems = 256;  // items of the automatic attention plan: one per compute unit
 struct AttnPlan {
-    int kv_split;     // tokens per split-KV work item (multiple of 64)
+    bool list;        // a list of items (many units, attn_list.hip), else ranges of equal cost (attn.hip)
+    int kv_split;     // tokens per work item: the caller's split, the list's, else the longest context
     int max_splits;   // ceil(max_kv_len / kv_split)
     int waves;        // waves per workgroup (bf16 path)
     int halves;       // 2: a wave owns a 32-token half of each tile, 1: the whole tile
     int row_blocks;   // query-row blocks of (waves / halves) * 32 rows per (request, kv-head)
-    size_t part_o_bytes;    // split partial outputs (fp32), offset 0
-    size_t part_lse_bytes;  // split partial log-sum-exps, after part_o
-    size_t off_groups;      // work list of the persistent kernel
-    size_t off_ctr;         // {number of work items, work counter, finished workgroups}
+    int ranges;       // most ranges of a plan per kv-head
+    int slot_rows;    // query rows of one partial result
+    size_t part_o_bytes;    // partial outputs (fp32), offset 0
+    size_t part_lse_bytes;  // partial log-sum-exps, after part_o
+    size_t off_groups;      // the list or the ranges of the plan
+    size_t off_pre;         // cost before each request (plans of many requests)
+    size_t off_ctr;         // {items or ranges, claim counter, finished workgroups}
     size_t ws_bytes;        // total workspace (0 for the fp32 path)
 };
 struct AcceptPlan {

@@ -7,6 +7,8 @@
 #include <cstddef>
 #include <cstdint>
 
+#include "attn_list_plan.h"
+#include "attn_plan.h"
 #include "specverify.h"
 #include "sv_host.h"
 
@@ -26,6 +28,8 @@ hipError_t launch_prepare(const sv_budget_desc& d, const float* conf, int32_t* k
 // ---- verify attention -----------------------------------------------------------
 // what launch_attn runs: the work plan, the attention (and the merge of split partials), or both
 enum AttnPhases { kAttnPlan = 1, kAttnRun = 2, kAttnAll = 3 };
+AttnPlanArgs attn_plan_args(const sv_attn_desc& d, const AttnPlan& plan, void* ws);
+AttnListArgs attn_list_args(const sv_attn_desc& d, const AttnPlan& plan, void* ws);
 hipError_t launch_attn(const sv_attn_desc& d, const AttnPlan& plan, const void* q,
                        const void* k_cache, const void* v_cache, const int32_t* page_table,
                        const int32_t* qo_indptr, const int32_t* kv_lens, void* out, float* lse,
