@@ -14,11 +14,11 @@
 // A unit that lies in one range is written directly; the pieces of a cut unit leave fp32
 // partials merged by a second kernel (log-sum-exp weights).
 //
-// Bound by the K/V stream up to 64 rows per kv-head group (7.0 of the 7.1 TB/s a plain read
-// reaches while a workgroup streams), by the softmax's vector work in whole-tile units; the rest
-// is the pieces' starts and, before, the uneven end. Measured against the sorted list of
-// attn_list.hip: 4 MTP requests (188 MB) 44.1 -> 41 us, 27 requests on pages of 16 (256 MB)
-// 65 -> 54 us, 32 requests of 65536..131072 tokens (6.45 GB) 1333 -> 1228 us.
+// Bound by the K/V stream up to 64 rows per kv-head group and by the softmax's vector work in
+// whole-tile units; the rest is the pieces' starts and, with a list of splits, the uneven end.
+// Measured, the list of attn_list.hip against this: 4 requests of 4 positions (188 MB) 44.4 and
+// 40.3 us, 27 requests on pages of 16 tokens (256 MB) 65.1 and 53.0 us, 32 requests of
+// 65536..131072 tokens (6.45 GB) 1342 and 1251 us.
 //
 // fp32 path (vector ALU): one workgroup per (query row, head); its four waves take
 // interleaved 64-key tiles and merge their softmax states at the end.

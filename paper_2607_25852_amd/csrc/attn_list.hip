@@ -9,7 +9,8 @@
 // kv-heads: 64 requests of 512..32768 tokens and 16 positions 274 against 280 us, 128 requests of
 // 256..16384 tokens and 5 positions 261 against 270 us; 32 requests of 512..65536 tokens 298
 // against 275 us, 16 requests of 1024..8192 tokens 69 against 60 us.
-// Bound by the K/V stream: 1.95 GB in the first case, 7.1 TB/s.
+// Bound by the K/V stream: 1.70 GB in the first case, 6.2 TB/s over the call, of the 7.1 TB/s that
+// a plain read reaches.
 #include <algorithm>
 
 #include "attn_list_plan.h"
