@@ -710,7 +710,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RangeArgs a, const Attn
         m = ~__ballot(rn.req == i && rn.block == block && b + lane < n);
         last += m ? __builtin_ctzll(m) : 64;
     }
-    if (k_i < 1 || k_i > a.block || q0 < 0 || q0 + k_i > a.total_q) return;  // (a plan of other inputs)
+    if (!rows_in_batch(q0, k_i, a.block, a.total_q)) return;  // (a plan of other inputs)
     const int row0 = block * rb_rows;
     const int M = min(a.G * k_i - row0, rb_rows);
     const int u = blockIdx.x * 256 + threadIdx.x;

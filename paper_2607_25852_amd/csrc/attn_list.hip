@@ -61,7 +61,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
     if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
     const int L = kv_len - k_i;
     // (bitwise or: both descriptor loads are issued before the test)
-    if ((k_i <= 0) | (k_i > a.block) | (L < 0) | (q0 < 0) | (q0 + k_i > a.total_q)) return;
+    if ((kv_len < k_i) | !rows_in_batch(q0, k_i, a.block, a.total_q)) return;
     const int tok_begin = s * a.split;
     if (tok_begin >= kv_len) return;
     const int tok_end = min(kv_len, tok_begin + a.split);
@@ -569,7 +569,7 @@ __global__ __launch_bounds__(256) void attn_list_merge_kernel(AttnArgs a) {
     const int q0 = a.qo[i], k_i = a.qo[i + 1] - q0;
     int kv_len = a.kv_lens[i];
     if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
-    if (k_i <= 0 || k_i > a.block || kv_len - k_i < 0 || q0 < 0 || q0 + k_i > a.total_q) return;
+    if (!rows_in_batch(q0, k_i, a.block, a.total_q) || kv_len < k_i) return;
     const int nsplit = (kv_len + a.split - 1) / a.split;
     if (nsplit <= 1) return;
     const int u = blockIdx.x * 256 + threadIdx.x;

@@ -28,7 +28,7 @@ struct AttnListArgs {
 __device__ inline int plan_splits(const AttnListArgs& a, int q0, int k_i, int kv_len, int& last_tiles) {
     if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
     last_tiles = 0;
-    if (!(k_i >= 1 && k_i <= a.block && kv_len - k_i >= 0 && q0 >= 0 && q0 + k_i <= a.total_q)) return 0;
+    if (!rows_in_batch(q0, k_i, a.block, a.total_q) || kv_len < k_i) return 0;
     const int ns = (kv_len + a.split - 1) / a.split;
     last_tiles = (kv_len - (ns - 1) * a.split + kAttnTile - 1) / kAttnTile;
     return ns;

@@ -16,6 +16,8 @@
 
 #include <cstdint>
 
+#include "rows.h"
+
 namespace sv {
 
 constexpr int kAttnTile = 64;       // KV tokens per tile of the attention kernel
@@ -55,7 +57,7 @@ struct AttnPlanArgs {
 // tiles of request i's context, 0 when its packing is malformed
 __device__ inline int plan_tiles(int block, int total_q, int max_kv_len, int q0, int k_i, int kv_len) {
     if (kv_len > max_kv_len) kv_len = max_kv_len;
-    if (!(k_i >= 1 && k_i <= block && kv_len - k_i >= 0 && q0 >= 0 && q0 + k_i <= total_q)) return 0;
+    if (!rows_in_batch(q0, k_i, block, total_q) || kv_len < k_i) return 0;
     return (kv_len + kAttnTile - 1) / kAttnTile;
 }
 

@@ -265,7 +265,7 @@ __global__ __launch_bounds__(NT) void budget_kernel(BudgetArgs a, const float* _
             const int i = p / b, j = p - i * b;
             const int q0 = qs[i], k_i = qs[i + 1] - q0;
             const int L = Lc[e];
-            const bool ok = k_i >= 1 && k_i <= b && q0 >= 0 && q0 + k_i <= pr.total_max;
+            const bool ok = rows_in_batch(q0, k_i, b, pr.total_max);
             if (j == 0) {
                 pr.kv_lens[i] = ok ? L + k_i : L;
                 kvs[i] = ok ? L + k_i : L;

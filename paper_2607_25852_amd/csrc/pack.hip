@@ -1,6 +1,7 @@
 // The dense verify batch of the kept prefixes (AngelSpec Sec. 4.2, packing) and the
 // append of their keys and values to the paged cache. Both are plain data movement:
 // integer index arithmetic and 16-byte copies, no floating point.
+#include "rows.h"
 #include "sv_internal.h"
 
 namespace sv {
@@ -23,7 +24,7 @@ __global__ __launch_bounds__(256) void pack_kernel(PackArgs a) {
     const int i = (int)(e / a.b), j = (int)(e % a.b);
     const int q0 = a.qo[i], k_i = a.qo[i + 1] - q0;
     const int L = a.ctx[i];
-    const bool ok = k_i >= 1 && k_i <= a.b && q0 >= 0 && q0 + k_i <= a.total_max;
+    const bool ok = rows_in_batch(q0, k_i, a.b, a.total_max);
     if (j == 0) a.kv_lens[i] = ok ? L + k_i : L;
     if (!ok || j >= k_i) return;
     a.tokens[q0 + j] = a.block_tokens[(size_t)i * a.b + j];
@@ -48,7 +49,7 @@ __global__ __launch_bounds__(128) void append_kernel(AppendArgs a) {
     const int e = blockIdx.x, h = blockIdx.y;
     const int i = e / a.block, j = e % a.block;
     const int q0 = a.qo[i], k_i = a.qo[i + 1] - q0;
-    if (k_i < 1 || k_i > a.block || j >= k_i || q0 < 0 || q0 + k_i > a.total_max) return;
+    if (j >= k_i || !rows_in_batch(q0, k_i, a.block, a.total_max)) return;
     const long long s = (long long)a.ctx[i] + j;  // position of the row in the sequence
     if (a.ctx[i] < 0) return;
     const long long col = s >> a.log2P;

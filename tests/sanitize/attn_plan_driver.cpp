@@ -1,0 +1,67 @@
+// Drives the device code that divides the verify attention's work (csrc/rows.h, attn_plan.h) on
+// the host, under AddressSanitizer and UndefinedBehaviorSanitizer without recovery: what a run
+// reads from a workspace that holds no plan is arbitrary, and no arithmetic on it may wrap past a
+// check.
+#include <climits>
+#include <cstdio>
+#include <cstdlib>
+
+#include "attn_plan.h"
+
+namespace {
+
+uint64_t g_state = 0x9E3779B97F4A7C15ull;
+uint64_t next_u64() {  // splitmix64
+    uint64_t z = (g_state += 0x9E3779B97F4A7C15ull);
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    return z ^ (z >> 31);
+}
+int below(int n) { return (int)(next_u64() % (uint64_t)n); }
+
+void expect(bool ok, const char* what) {
+    if (!ok) {
+        std::fprintf(stderr, "FAILED: %s\n", what);
+        std::exit(2);
+    }
+}
+
+const int kWords[] = {INT_MIN, INT_MIN + 1, -65536, -16, -1, 0, 1, 2, 3, 15, 16, 17, 63, 64, 65, 1000, 65536,
+                      1 << 22, INT_MAX - 16, INT_MAX - 1, INT_MAX};
+constexpr int kNumWords = sizeof(kWords) / sizeof(kWords[0]);
+
+// a word as garbage or a stale plan may hold it
+int word(int near) {
+    switch (below(4)) {
+        case 0: return kWords[below(kNumWords)];
+        case 1: return (int)(uint32_t)next_u64();
+        default: return below(2 * near + 2) - 1;
+    }
+}
+
+// ---- the row and length checks at every extreme, against 64-bit arithmetic ----
+void check_ranges_of_words() {
+    for (int q0 : kWords)
+        for (int k : kWords)
+            for (int total : kWords)
+                for (int block : {1, 5, 16}) {
+                    const bool in = k >= 1 && k <= block && q0 >= 0 && (long long)q0 + k <= total;
+                    expect(sv::rows_in_batch(q0, k, block, total) == in, "rows_in_batch");
+                    if (total < 1) continue;  // (a descriptor's total is positive)
+                    for (int kv : kWords)
+                        for (int cap : {1, 64, 65, 1 << 22}) {
+                            const long long n = kv > cap ? cap : kv;
+                            const long long want = in && n >= k ? (n + 63) / 64 : 0;
+                            expect(sv::plan_tiles(block, total, cap, q0, k, kv) == want, "plan_tiles");
+                        }
+                }
+}
+
+}  // namespace
+
+int main() {
+    check_ranges_of_words();
+    (void)word;
+    std::printf("ok\n");
+    return 0;
+}
