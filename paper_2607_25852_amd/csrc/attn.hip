@@ -626,7 +626,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, cons
     // the number of ranges is capped by what the workspace holds, a claim outside it ends the
     // loop, and a cut that names no request, unit or tile is skipped, so every access stays in
     // bounds and every loop ends (the results are then unspecified).
-    const int n = min(ctr[0], a.ranges) * a.Hkv;  // (below 2^31: checked on the host)
+    const int n = plan_ranges(ctr[0], a.ranges) * a.Hkv;  // (below 2^31: checked on the host)
     constexpr int RB = WIDE ? NW * 32 : NW * 16;
     int item = blockIdx.x, claim = 0;
     for (;;) {
@@ -694,7 +694,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RangeArgs a, const Attn
     constexpr int SL = HD / 4;  // 4-dim slices per row
     // one round of loads: the number of ranges, this cut, the one before and the 62 after
     const int c = c0 + blockIdx.z + 1, h = blockIdx.y, lane = threadIdx.x & 63;
-    const int n = min(ctr[0], a.ranges);
+    const int n = plan_ranges(ctr[0], a.ranges);
     const AttnRange mine = recs[min(c - 1 + lane, a.ranges)];
     if (c >= n) return;
     auto at = [&](int v, int l) { return __builtin_amdgcn_readlane(v, l); };

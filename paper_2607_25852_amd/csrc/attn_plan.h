@@ -54,6 +54,10 @@ struct AttnPlanArgs {
     int32_t* ctr;      // {ranges per head, claim counter, finished workgroups}
 };
 
+// ranges per head of a plan whose count reads `stored` (any word, where no plan was built): never
+// negative, so that its product with the heads is at most that of `most`, which the host checks
+__device__ inline int plan_ranges(int stored, int most) { return stored < 0 ? 0 : stored < most ? stored : most; }
+
 // tiles of request i's context, 0 when its packing is malformed
 __device__ inline int plan_tiles(int block, int total_q, int max_kv_len, int q0, int k_i, int kv_len) {
     if (kv_len > max_kv_len) kv_len = max_kv_len;

@@ -57,11 +57,22 @@ void check_ranges_of_words() {
                 }
 }
 
+// ---- the number of items of any stored count: within the items of the longest plan ----
+void check_item_counts() {
+    for (int it = 0; it < 100000; it++) {
+        const int heads = 1 + below(511), most = 1 + below(0x7FFFFFF0 / heads);
+        const int stored = word(most < 1 << 20 ? most : 1 << 20);
+        const int n = sv::plan_ranges(stored, most) * heads;
+        expect(n >= 0 && n <= most * heads, "item count");
+        if (stored >= 0 && stored <= most) expect(n == stored * heads, "a built plan keeps its count");
+    }
+}
+
 }  // namespace
 
 int main() {
     check_ranges_of_words();
-    (void)word;
+    check_item_counts();
     std::printf("ok\n");
     return 0;
 }
