@@ -623,9 +623,9 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, cons
     __shared__ __attribute__((aligned(16))) LdsRing<HD, NBUF> lds;
     __shared__ int s_item;
     // A plan that was never built (a run on a workspace without one) holds arbitrary values:
-    // the number of ranges is capped by what the workspace holds, a claim outside it ends the
-    // loop, and a cut that names no request, unit or tile is skipped, so every access stays in
-    // bounds and every loop ends (the results are then unspecified).
+    // the number of ranges is clamped to what the workspace holds, a claim outside it ends the
+    // loop, and walk_range passes existing pieces only, so every access stays in bounds and every
+    // loop ends (the results are then unspecified).
     const int n = plan_ranges(ctr[0], a.ranges) * a.Hkv;  // (below 2^31: checked on the host)
     constexpr int RB = WIDE ? NW * 32 : NW * 16;
     int item = blockIdx.x, claim = 0;
@@ -648,30 +648,18 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, cons
         const int rng = seq / a.Hkv, h = seq % a.Hkv;
         if (seq >= n) return;
         const AttnRange r0 = recs[rng], r1 = recs[rng + 1];
-        int rb = r0.block, t = r0.tile;
-        for (int i = max(r0.req, 0); i <= r1.req && i < a.R; i++, rb = 0, t = 0) {
-            int q0 = r0.q0, k_i = r0.k, kv_len = r0.kv;
-            if (i != r0.req) {
-                q0 = a.qo[i];
-                k_i = a.qo[i + 1] - q0;
-                kv_len = a.kv_lens[i];
-            }
-            kv_len = min(kv_len, a.max_kv_len);
-            const int nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv_len);
-            if (nt == 0) continue;
-            const int rb_end = i == r1.req ? min(r1.block, a.nrb - 1) : a.nrb - 1;  // (the last unit, cut or whole)
-            for (rb = max(rb, 0); rb <= rb_end; rb++, t = 0) {
-                const int row0 = rb * RB;
-                const int t0 = max(t, 0), t1 = i == r1.req && rb == r1.block ? min(r1.tile, nt) : nt;
-                if (t0 >= t1 || a.G * k_i <= row0) continue;
-                const int slot = 2 * (rng * a.Hkv + h) + (t0 == 0);
-                if (WIDE && a.G * k_i - row0 > NW * 16)
-                    attn_item<HD, NW, NBUF, PM, 1>(a, lds, i, h, row0, q0, k_i, kv_len, t0, t1, nt, slot);
-                else
-                    attn_item<HD, NW, NBUF, PM, 2>(a, lds, i, h, row0, q0, k_i, kv_len, t0, t1, nt, slot);
-                __syncthreads();  // the LDS of this piece is free
-            }
-        }
+        walk_range(a, r0, r1, RB, [&](int i, int& q0, int& k_i, int& kv_len) {
+            q0 = a.qo[i];
+            k_i = a.qo[i + 1] - q0;
+            kv_len = a.kv_lens[i];
+        }, [&](int i, int row0, int q0, int k_i, int kv_len, int t0, int t1, int nt) {
+            const int slot = 2 * (rng * a.Hkv + h) + (t0 == 0);
+            if (WIDE && a.G * k_i - row0 > NW * 16)
+                attn_item<HD, NW, NBUF, PM, 1>(a, lds, i, h, row0, q0, k_i, kv_len, t0, t1, nt, slot);
+            else
+                attn_item<HD, NW, NBUF, PM, 2>(a, lds, i, h, row0, q0, k_i, kv_len, t0, t1, nt, slot);
+            __syncthreads();  // the LDS of this piece is free
+        });
         if (n <= (int)gridDim.x) return;
         claim = 1;
     }

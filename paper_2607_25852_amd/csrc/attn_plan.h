@@ -184,4 +184,33 @@ __device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint64_
     }
 }
 
+// Calls piece(i, row0, q0, k_i, kv_len, t0, t1, nt) for each piece of the range between two cuts:
+// request i's rows from row0 of the kv-head group on (row block row0 / rb_rows) against tiles
+// t0 .. t1-1 of the nt tiles of its context. req(i, q0, k_i, kv_len) gives the packing and key
+// count of the requests after the first, which the cut itself carries. The cuts may hold any
+// words: every piece lies in its request, its request in the batch, and where a plan has one range
+// (and the workspace no partial results) every piece is a whole unit.
+template <typename Args, typename ReqFn, typename PieceFn>
+__device__ __forceinline__ void walk_range(const Args& a, const AttnRange& r0, const AttnRange& r1, int rb_rows,
+                                           ReqFn req, PieceFn piece) {
+    const bool cuts = a.ranges > 1;
+    int rb = r0.block, t = r0.tile;
+    for (int i = r0.req > 0 ? r0.req : 0; i <= r1.req && i < a.R; i++, rb = 0, t = 0) {
+        int q0 = r0.q0, k_i = r0.k, kv_len = r0.kv;
+        if (i != r0.req) req(i, q0, k_i, kv_len);
+        if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
+        const int nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv_len);
+        if (nt == 0) continue;
+        // (the last unit, cut or whole)
+        const int rb_end = i == r1.req && r1.block < a.nrb ? r1.block : a.nrb - 1;
+        for (rb = rb > 0 ? rb : 0; rb <= rb_end; rb++, t = 0) {
+            const int row0 = rb * rb_rows;
+            const int t0 = cuts && t > 0 ? t : 0;
+            const int t1 = cuts && i == r1.req && rb == r1.block && r1.tile < nt ? r1.tile : nt;
+            if (t0 >= t1 || a.G * k_i <= row0) continue;
+            piece(i, row0, q0, k_i, kv_len, t0, t1, nt);
+        }
+    }
+}
+
 }  // namespace sv

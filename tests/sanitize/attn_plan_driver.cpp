@@ -32,7 +32,7 @@ constexpr int kNumWords = sizeof(kWords) / sizeof(kWords[0]);
 
 // a word as garbage or a stale plan may hold it
 int word(int near) {
-    switch (below(4)) {
+    switch (below(16)) {
         case 0: return kWords[below(kNumWords)];
         case 1: return (int)(uint32_t)next_u64();
         default: return below(2 * near + 2) - 1;
@@ -68,11 +68,57 @@ void check_item_counts() {
     }
 }
 
+struct Shape {
+    int R, block, total_q, max_kv_len, G, nrb, ranges;
+};
+
+// ---- the walk between cuts of arbitrary words: existing rows and tiles only ----
+void check_walk_of_words() {
+    long pieces = 0;
+    for (int it = 0; it < 200000; it++) {
+        Shape a{};
+        a.R = 1 + below(6);
+        a.block = 1 + below(16);
+        a.total_q = 1 + below(a.R * a.block);
+        a.max_kv_len = it % 2 ? 1 + below(300) : 1 << below(23);
+        a.G = 1 + below(16);
+        const int rb_rows = a.G * a.block > 128 ? 256 : 128;
+        a.nrb = (a.G * a.block + rb_rows - 1) / rb_rows;
+        a.ranges = 1 + below(3);
+        const int tiles = (a.max_kv_len + 63) / 64;
+        auto cut = [&] {
+            return sv::AttnRange{word(a.R), word(a.nrb), word(tiles), word(a.total_q), word(a.block),
+                                 word(a.max_kv_len), word(1), word(1)};
+        };
+        const sv::AttnRange r0 = cut(), r1 = cut();
+        const int q_of = word(a.total_q), k_of = word(a.block), kv_of = word(a.max_kv_len);
+        int calls = 0;
+        sv::walk_range(a, r0, r1, rb_rows, [&](int i, int& q0, int& k_i, int& kv) {
+            expect(i >= 0 && i < a.R, "request");
+            q0 = q_of;
+            k_i = k_of;
+            kv = kv_of;
+        }, [&](int i, int row0, int q0, int k_i, int kv, int t0, int t1, int nt) {
+            calls++;
+            pieces++;
+            expect(i >= 0 && i < a.R, "request of a piece");
+            expect(k_i >= 1 && k_i <= a.block && q0 >= 0 && (long long)q0 + k_i <= a.total_q, "rows");
+            expect(row0 >= 0 && row0 % rb_rows == 0 && row0 < a.G * k_i, "first row");
+            expect(kv >= k_i && kv <= a.max_kv_len && nt == (kv + 63) / 64, "keys");
+            expect(t0 >= 0 && t0 < t1 && t1 <= nt, "tiles");
+            expect(a.ranges > 1 || t1 - t0 == nt, "one range has no partial results to write to");
+        });
+        expect(calls <= a.R * a.nrb, "number of pieces");
+    }
+    expect(pieces > 10000, "the words gave pieces");
+}
+
 }  // namespace
 
 int main() {
     check_ranges_of_words();
     check_item_counts();
+    check_walk_of_words();
     std::printf("ok\n");
     return 0;
 }
