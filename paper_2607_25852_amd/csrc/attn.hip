@@ -616,7 +616,7 @@ __global__ __launch_bounds__(1024) void attn_plan_kernel(RangeArgs a, AttnPlanAr
 }
 
 // Persistent kernel: a workgroup takes the item of its own index, then claims further ones
-// from a counter when the plan has more items than the grid has workgroups.
+// from a counter when the grid does not take all items in one pass.
 template <int HD, int NW, int NBUF, PageMode PM, bool WIDE>
 __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, const AttnRange* __restrict__ recs,
                                                                int32_t* __restrict__ ctr) {
@@ -628,25 +628,21 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, cons
     // loop ends (the results are then unspecified).
     const int n = plan_ranges(ctr[0], a.ranges) * a.Hkv;  // (below 2^31: checked on the host)
     constexpr int RB = WIDE ? NW * 32 : NW * 16;
-    int item = blockIdx.x, claim = 0;
+    const bool one_pass = plan_one_pass(n, gridDim.x);
+    int index = blockIdx.x, claim = 0;
     for (;;) {
         // (opaque to the compiler, so that the claim stays at the head of the loop, in one
         // loop with its barriers)
         asm volatile("" : "+s"(claim));
         if (claim) {
-            if (threadIdx.x == 0) s_item = (int)gridDim.x + atomicAdd(&ctr[1], 1);
+            if (threadIdx.x == 0) s_item = (int)(gridDim.x + (unsigned)atomicAdd(&ctr[1], 1));
             __syncthreads();
-            item = s_item;
+            index = s_item;
             __syncthreads();
         }
-        if (item < 0 || item >= (n <= (int)gridDim.x ? (n + 7) / 8 * 8 : n)) break;
-        // Workgroups go to the 8 XCDs round-robin: each XCD takes a contiguous part of the items,
-        // so that the heads of a range, whose K/V blocks are neighbours in every page, run on one
-        // XCD and share its address translations.
-        const int per_xcd = (n + 7) / 8;
-        const int seq = n <= (int)gridDim.x ? (item % 8) * per_xcd + item / 8 : item;
-        const int rng = seq / a.Hkv, h = seq % a.Hkv;
-        if (seq >= n) return;
+        const int item = plan_item(index, n, one_pass);
+        if (item < 0) break;
+        const int rng = item / a.Hkv, h = item % a.Hkv;
         const AttnRange r0 = recs[rng], r1 = recs[rng + 1];
         walk_range(a, r0, r1, RB, [&](int i, int& q0, int& k_i, int& kv_len) {
             q0 = a.qo[i];
@@ -660,13 +656,13 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, cons
                 attn_item<HD, NW, NBUF, PM, 2>(a, lds, i, h, row0, q0, k_i, kv_len, t0, t1, nt, slot);
             __syncthreads();  // the LDS of this piece is free
         });
-        if (n <= (int)gridDim.x) return;
+        if (one_pass) return;
         claim = 1;
     }
     // the last workgroup to finish leaves the counters as the plan left them, so the
     // next call on the same plan (another layer of the round) starts clean: every
     // workgroup has made its last claim before it counts itself here
-    if (n > (int)gridDim.x && threadIdx.x == 0 && atomicAdd(&ctr[2], 1) == (int)gridDim.x - 1) {
+    if (!one_pass && threadIdx.x == 0 && atomicAdd(&ctr[2], 1) == (int)gridDim.x - 1) {
         ctr[1] = 0;
         ctr[2] = 0;
     }

@@ -184,6 +184,22 @@ __device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint64_
     }
 }
 
+// A grid takes n items in one pass when it has a workgroup for each of them on every XCD, that is
+// for 8 * ceil(n / 8) of them; else its workgroups go on claiming items.
+__device__ inline bool plan_one_pass(int n, int grid) { return n <= grid / 8 * 8; }
+
+// The item of workgroup (or claim) `index`, -1 past the last. Workgroups go to the 8 XCDs
+// round-robin: in one pass each XCD takes a contiguous part of the items, so that the heads of a
+// range, whose K/V blocks are neighbours in every page, run on one XCD and share its address
+// translations.
+__device__ inline int plan_item(int index, int n, bool one_pass) {
+    if (index < 0) return -1;
+    if (!one_pass) return index < n ? index : -1;
+    const int per_xcd = (n + 7) / 8;
+    const int item = (index % 8) * per_xcd + index / 8;
+    return index / 8 < per_xcd && item < n ? item : -1;
+}
+
 // Calls piece(i, row0, q0, k_i, kv_len, t0, t1, nt) for each piece of the range between two cuts:
 // request i's rows from row0 of the kv-head group on (row block row0 / rb_rows) against tiles
 // t0 .. t1-1 of the nt tiles of its context. req(i, q0, k_i, kv_len) gives the packing and key

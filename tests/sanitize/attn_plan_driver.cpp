@@ -68,6 +68,29 @@ void check_item_counts() {
     }
 }
 
+// ---- every item is taken by exactly one workgroup, whatever the grid ----
+void check_items_of_grids() {
+    for (int grid = 1; grid <= 320; grid++)
+        for (int n = 0; n <= 2 * grid + 9; n++) {
+            const bool one_pass = sv::plan_one_pass(n, grid);
+            std::vector<int> seen(n, 0);
+            // without one pass, the claims follow the workgroups' own indices without a gap
+            for (int index = 0; index < (one_pass ? grid : n + grid); index++) {
+                const int item = sv::plan_item(index, n, one_pass);
+                expect(item >= -1 && item < n, "an existing item");
+                if (item >= 0) seen[item]++;
+            }
+            for (int i = 0; i < n; i++) expect(seen[i] == 1, "each item once");
+        }
+    for (int w : kWords)
+        for (int n : {0, 1, 255, 256, 257, 0x7FFFFFF0})
+            for (bool one_pass : {false, true}) {
+                const int item = sv::plan_item(w, n, one_pass && sv::plan_one_pass(n, 256));
+                expect(item >= -1 && item < n, "an existing item for any claim");
+            }
+    expect(sv::plan_one_pass(256, 256) && !sv::plan_one_pass(0x7FFFFFF0, 256), "one pass");
+}
+
 struct Shape {
     int R, block, total_q, max_kv_len, G, nrb, ranges;
 };
@@ -118,6 +141,7 @@ void check_walk_of_words() {
 int main() {
     check_ranges_of_words();
     check_item_counts();
+    check_items_of_grids();
     check_walk_of_words();
     std::printf("ok\n");
     return 0;
