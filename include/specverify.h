@@ -202,7 +202,8 @@ typedef struct {
     int32_t max_kv_len;        /* upper bound of kv_lens[i], <= 2^22                  */
     int32_t dtype;             /* sv_dtype of q, caches and out                       */
     float sm_scale;            /* logit scale; 0 means 1/sqrt(d)                      */
-    int32_t kv_split;          /* tokens per work item (multiple of 64), 0 = auto */
+    int32_t kv_split;          /* tokens of a request per work item (multiple of 64;
+                                  at most 1022 pages are taken), 0 = auto            */
 } sv_attn_desc;
 
 /*
@@ -223,6 +224,11 @@ typedef struct {
  *            the work plan of the persistent kernel and the partial results of
  *            contexts cut into several work items; fp32: none), device memory, overwritten by every call.
  * bf16 runs on MFMA with fp32 accumulation; fp32 runs on vector ALUs in fp32.
+ * The same call on the same inputs gives the same bits. In bf16 the rounding of a request's
+ * results also depends on where its context is divided: with kv_split = 0 that follows the
+ * descriptor's sizes and may follow the lengths of the whole batch; with a given kv_split it is
+ * the request's own (equal bits in any batch whose descriptor differs in num_reqs and
+ * total_q_max only). fp32 results never depend on the batch.
  */
 sv_status sv_verify_attn(const sv_attn_desc* desc, const void* q, const void* k_cache,
                          const void* v_cache, const int32_t* page_table, const int32_t* qo_indptr,

@@ -1,12 +1,13 @@
 // Verify attention over a paged KV cache (AngelSpec Sec. 4.1: every kept block
 // position is evaluated by the target model; Sec. 4.2: one dense packed batch).
 //
-// bf16 path (MFMA), for fewer than two (request, kv-head, row block) units per compute unit; from
-// there on a list of items does as well or better (attn_list.hip). The plan (attn_plan.h) cuts the line of all (request, row block) units
-// of a kv-head into ranges by cost; a workgroup takes one range of one head at a time and
-// processes its pieces: the query rows of a unit against a run of 64-token tiles of the
-// request's context. Query rows go on the N side of the MFMA and KV tokens
-// on the M side, so S^T = K Q^T puts all scores of one query row in one lane pair:
+// bf16 path (MFMA), for fewer than two (request, kv-head, row block) units per compute unit and no
+// given split size; from there on a list of items does as well or better (attn_list.hip). The plan
+// (attn_plan.h) cuts the line of all (request, row block) units of a kv-head into ranges by cost;
+// a workgroup takes one range of one head at a time and processes its pieces: the query rows of a
+// unit against a run of 64-token tiles of the request's context. Query rows go on the N side of
+// the MFMA and KV tokens on the M side, so S^T = K Q^T puts all scores of one query row in one
+// lane pair:
 // the online-softmax max/sum is lane-local plus one cross-half swap. The P^T
 // fragment is then already in the B-operand layout of O^T = V^T P^T; V is staged
 // transposed in LDS to serve the A operand. K and V tiles of 64 tokens are
@@ -674,10 +675,10 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, cons
 // are loaded before any math.
 template <int HD, bool BF16OUT>
 __global__ __launch_bounds__(256) void attn_merge_kernel(RangeArgs a, const AttnRange* __restrict__ recs,
-                                                         const int32_t* __restrict__ ctr, int rb_rows, int c0) {
+                                                         const int32_t* __restrict__ ctr, int rb_rows) {
     constexpr int SL = HD / 4;  // 4-dim slices per row
     // one round of loads: the number of ranges, this cut, the one before and the 62 after
-    const int c = c0 + blockIdx.z + 1, h = blockIdx.y, lane = threadIdx.x & 63;
+    const int c = blockIdx.z + 1, h = blockIdx.y, lane = threadIdx.x & 63;
     const int n = plan_ranges(ctr[0], a.ranges);
     const AttnRange mine = recs[min(c - 1 + lane, a.ranges)];
     if (c >= n) return;
@@ -879,7 +880,6 @@ AttnPlanArgs attn_plan_args(const sv_attn_desc& d, const AttnPlan& p, void* ws) 
     char* w = (char*)ws;
     return AttnPlanArgs{d.num_reqs, d.block, d.total_q_max, d.max_kv_len, d.num_q_heads / d.num_kv_heads,
                         p.row_blocks, (p.waves / p.halves) * 32, p.ranges,
-                        d.kv_split > 0 ? p.kv_split / kAttnTile : 0,
                         d.num_kv_heads, (AttnRange*)(w + p.off_groups),
                         (uint64_t*)(w + p.off_pre), (int32_t*)(w + p.off_ctr)};
 }
@@ -972,16 +972,11 @@ hipError_t launch_attn(const sv_attn_desc& d, const AttnPlan& plan, const void* 
 #undef SV_LAUNCH_ATTN
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || plan.ranges <= 1) return e;
-    // (grids y and z are limited to 65535: more cuts than that come from tiny split sizes only;
-    // more heads are refused)
-    for (int c0 = 0; c0 < plan.ranges - 1; c0 += 65535) {
-        const dim3 mgrid((plan.slot_rows * (d.head_dim / 4) + 255) / 256, d.num_kv_heads,
-                         std::min(plan.ranges - 1 - c0, 65535));
-        if (d.head_dim == 128)
-            hipLaunchKernelGGL((attn_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows, c0);
-        else
-            hipLaunchKernelGGL((attn_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows, c0);
-    }
+    const dim3 mgrid((plan.slot_rows * (d.head_dim / 4) + 255) / 256, d.num_kv_heads, plan.ranges - 1);
+    if (d.head_dim == 128)
+        hipLaunchKernelGGL((attn_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows);
+    else
+        hipLaunchKernelGGL((attn_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows);
     return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
-// Work list of the persistent verify-attention kernel for calls of many units (attn_list.hip),
-// built by one workgroup. Every
-// (request, split) group is bucketed by its tile count: full splits share the top bucket,
+// Work list of the persistent verify-attention kernel for calls of many units or with a given
+// split size (attn_list.hip), built by one workgroup. Every (request, split) group is bucketed by its tile count: full splits share the top bucket,
 // a request's shorter last split lands in the bucket of its own length. The buckets are
 // laid out in decreasing size (a counting sort), so the persistent workgroups take the
 // long items early and the short ones fill the tail. The order inside a bucket is

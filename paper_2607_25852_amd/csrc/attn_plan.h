@@ -8,7 +8,6 @@
 // combines; an uncut unit is written directly. So the chip is filled evenly whatever the
 // lengths are, and at most one unit per cut needs a merge. The heads of a range are
 // neighbouring items, which run at the same time and read the same pages.
-// With a split size given by the caller the ranges are that many tokens long instead.
 // Used by the attention call's own plan kernel and by the round set-up kernel
 // (sv_prepare_round), so both build the same plan.
 #pragma once
@@ -47,7 +46,6 @@ struct AttnPlanArgs {
     int R, block, total_q, max_kv_len, G, nrb;
     int rb_rows;       // query rows per row block
     int ranges;        // most ranges per head the workspace holds
-    int range_tiles;   // tiles per range (a split size was given), or 0: ranges of equal cost
     int heads;         // kv-heads
     AttnRange* recs;   // [ranges + 1]
     uint64_t* pre;     // [R + 1] cost before each request, used above kPlanLdsReqs requests
@@ -66,19 +64,15 @@ __device__ inline int plan_tiles(int block, int total_q, int max_kv_len, int q0,
 }
 
 // cost per tile and of the start of a unit with M query rows
-__device__ inline unsigned plan_tile_cost(const AttnPlanArgs& a, int M) {
-    return a.range_tiles ? 1u : M > 128 ? kCostWideTile : M > 64 ? kCostTile65 : kCostTile;
-}
-__device__ inline unsigned plan_start_cost(const AttnPlanArgs& a, int M) {
-    return a.range_tiles ? 0u : M > 64 ? kCostStart65 : kCostStart;
-}
-__device__ inline unsigned plan_unit_cost(const AttnPlanArgs& a, int M, int nt) {
+__device__ inline unsigned plan_tile_cost(int M) { return M > 128 ? kCostWideTile : M > 64 ? kCostTile65 : kCostTile; }
+__device__ inline unsigned plan_start_cost(int M) { return M > 64 ? kCostStart65 : kCostStart; }
+__device__ inline unsigned plan_unit_cost(int M, int nt) {
     if (M <= 0 || nt <= 0) return 0;
-    return plan_start_cost(a, M) + (unsigned)nt * plan_tile_cost(a, M);
+    return plan_start_cost(M) + (unsigned)nt * plan_tile_cost(M);
 }
 __device__ inline unsigned plan_head_cost(const AttnPlanArgs& a, int k_i, int nt) {
     unsigned c = 0;
-    for (int rb = 0; rb < a.nrb; rb++) c += plan_unit_cost(a, a.G * k_i - rb * a.rb_rows, nt);
+    for (int rb = 0; rb < a.nrb; rb++) c += plan_unit_cost(a.G * k_i - rb * a.rb_rows, nt);
     return c;
 }
 
@@ -125,21 +119,15 @@ __device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint64_
     if (tid == 0) pre[a.R] = W;
     __syncthreads();
     // 2. the size of the ranges
-    const bool automatic = a.range_tiles == 0;
-    uint64_t step;
-    if (automatic) {
-        const uint64_t least = kCostStart + kPlanMinTiles * kCostTile;
-        const uint64_t up = W + (unsigned)a.ranges - 1;
-        step = up >> 32 ? up / (unsigned)a.ranges : (unsigned)up / (unsigned)a.ranges;
-        if (step < least) step = least;
-    } else {
-        step = (uint64_t)a.range_tiles;
-    }
+    const uint64_t least = kCostStart + kPlanMinTiles * kCostTile;
+    const uint64_t up = W + (unsigned)a.ranges - 1;
+    uint64_t step = up >> 32 ? up / (unsigned)a.ranges : (unsigned)up / (unsigned)a.ranges;
+    if (step < least) step = least;
     const uint64_t upto = W + step - 1;
     const uint64_t want = upto >> 32 || step >> 32 ? upto / step : (unsigned)upto / (unsigned)step;
     const int n = want < (uint64_t)a.ranges ? (int)want : a.ranges;
     // the items of a range share an XCD when its workgroups hold whole ranges (attn.hip)
-    const bool skewed = automatic && n % 8 == 0 && n * a.heads <= kPlanGrid;
+    const bool skewed = n % 8 == 0 && n * a.heads <= kPlanGrid;
     // 3. the cuts: the request by binary search over the costs, then row block and tile
     for (int r = tid; r <= n; r += NT) {
         uint64_t at = (uint64_t)r * step;
@@ -160,16 +148,16 @@ __device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint64_
             const int nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv);
             unsigned x = (unsigned)(at - pre[lo]);
             int rb = 0;
-            unsigned uc = plan_unit_cost(a, a.G * k_i, nt);
+            unsigned uc = plan_unit_cost(a.G * k_i, nt);
             while (x >= uc && rb + 1 < a.nrb) {
                 x -= uc;
                 rb++;
-                uc = plan_unit_cost(a, a.G * k_i - rb * a.rb_rows, nt);
+                uc = plan_unit_cost(a.G * k_i - rb * a.rb_rows, nt);
             }
-            const unsigned start = plan_start_cost(a, a.G * k_i - rb * a.rb_rows);
-            int t = x > start ? (int)((x - start) / plan_tile_cost(a, a.G * k_i - rb * a.rb_rows)) : 0;
-            if (automatic && t <= kPlanSnapTiles) t = 0;
-            if (t >= nt || (automatic && nt - t <= kPlanSnapTiles && t > 0)) {
+            const unsigned start = plan_start_cost(a.G * k_i - rb * a.rb_rows);
+            int t = x > start ? (int)((x - start) / plan_tile_cost(a.G * k_i - rb * a.rb_rows)) : 0;
+            if (t <= kPlanSnapTiles) t = 0;
+            if (t >= nt || (nt - t <= kPlanSnapTiles && t > 0)) {
                 t = 0;
                 rb++;
             }

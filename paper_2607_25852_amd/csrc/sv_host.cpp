@@ -214,9 +214,10 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
         return p;
     }
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    // Two units per compute unit and more: a work list (attn_list.hip, with what either side
-    // measured).
-    if ((long long)d.num_reqs * d.num_kv_heads * p.row_blocks >= 2 * kAttnItems) {
+    // A split size given by the caller, and two units per compute unit or more: a work list
+    // (attn_list.hip, with what either side measured). Its splits are each request's own, so that
+    // with a given size a request's results do not depend on the rest of the batch.
+    if (d.kv_split > 0 || (long long)d.num_reqs * d.num_kv_heads * p.row_blocks >= 2 * kAttnItems) {
         p.list = true;
         int split = d.kv_split;
         if (split <= 0) {
@@ -251,18 +252,16 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
         return p;
     }
     // The plan (attn_plan.h) cuts each kv-head's work into ranges: as many as give all heads
-    // together one item per compute unit (no more than the longest contexts hold tiles) or,
-    // when the caller gives a split size, ranges of that many tokens. Head counts that would
-    // leave over a tenth of the compute units without an item get about four items per unit.
+    // together one item per compute unit (no more than the longest contexts hold tiles). Head
+    // counts that would leave over a tenth of the compute units without an item get about four
+    // items per unit.
     const int hkv = d.num_kv_heads;
     int per_head = hkv <= kAttnItems ? kAttnItems / hkv : 0;
     if (per_head * hkv * 10 < kAttnItems * 9) per_head = (4 * kAttnItems + hkv - 1) / hkv;
     const long long whole = ((long long)d.max_kv_len + 63) / 64 * 64;
-    p.kv_split = d.kv_split > 0 && d.kv_split < whole ? d.kv_split : (int)whole;
-    p.max_splits = (d.max_kv_len + p.kv_split - 1) / p.kv_split;
-    const long long units = (long long)d.num_reqs * p.row_blocks;
-    const long long most = d.kv_split > 0 ? units * p.max_splits : std::min<long long>(per_head, units * (whole / 64));
-    p.ranges = (int)std::min<long long>(most, 0x7FFFFFF0LL / d.num_kv_heads);  // (items fit an int)
+    p.kv_split = (int)whole;
+    p.max_splits = 1;
+    p.ranges = (int)std::min<long long>(per_head, (long long)d.num_reqs * p.row_blocks * (whole / 64));
     p.slot_rows = std::min(maxM, rows);
     if (p.ranges > 1) {  // two partial results per item: a unit that continues into it and one that starts there
         const size_t slots = 2 * (size_t)p.ranges * d.num_kv_heads * p.slot_rows;

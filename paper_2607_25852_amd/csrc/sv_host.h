@@ -28,8 +28,8 @@ struct ReqPlan {
 // ---- workspace layouts --------------------------------------------------------------
 constexpr int kAttnItems = 256;  // items of the automatic attention plan: one per compute unit
 struct AttnPlan {
-    bool list;        // a list of items (many units, attn_list.hip), else ranges of equal cost (attn.hip)
-    int kv_split;     // tokens per work item: the caller's split, the list's, else the longest context
+    bool list;        // a list of items (many units or a given split, attn_list.hip), else ranges of equal cost (attn.hip)
+    int kv_split;     // list: tokens per work item, the caller's or chosen; ranges: the longest context
     int max_splits;   // ceil(max_kv_len / kv_split)
     int waves;        // waves per workgroup (bf16 path)
     int halves;       // 2: a wave owns a 32-token half of each tile, 1: the whole tile
