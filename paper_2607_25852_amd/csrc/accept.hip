@@ -299,7 +299,7 @@ __device__ inline ReqPlan decide_req(const AcceptArgs& a, const int i, const int
     const int n = a.qo[i + 1] - q0 - 1;
     const int K = a.qo[a.R];
     ReqPlan pl{};
-    if (n < 0 || n > a.D || K > a.R * a.b || !rows_in_batch(q0, n + 1, a.b, K)) {  // malformed packing: nothing to draw
+    if (K < 0 || K > a.R * a.b || n < 0 || n > a.D || !rows_in_batch(q0, n + 1, a.b, K)) {  // malformed packing: nothing to draw
         pl.mode = 2;
         pl.flag = 2;
         if (write) {
@@ -905,7 +905,7 @@ __global__ __launch_bounds__(64) void decide_greedy_kernel(AcceptArgs a) {
     const int q0 = a.qo[i];
     const int n = a.qo[i + 1] - q0 - 1;
     const int K = a.qo[a.R];
-    if (n < 0 || n > a.D || K > a.R * a.b || !rows_in_batch(q0, n + 1, a.b, K)) {  // malformed packing
+    if (K < 0 || K > a.R * a.b || n < 0 || n > a.D || !rows_in_batch(q0, n + 1, a.b, K)) {  // malformed packing
         if (lane == 0) {
             a.accept_len[i] = 0;
             if (a.flags) a.flags[i] = 2;

@@ -59,8 +59,8 @@ __device__ inline int plan_ranges(int stored, int most) { return stored < 0 ? 0 
 // tiles of request i's context, 0 when its packing is malformed
 __device__ inline int plan_tiles(int block, int total_q, int max_kv_len, int q0, int k_i, int kv_len) {
     if (kv_len > max_kv_len) kv_len = max_kv_len;
-    if (!rows_in_batch(q0, k_i, block, total_q) || kv_len < k_i) return 0;
-    return (kv_len + kAttnTile - 1) / kAttnTile;
+    const int nt = (int)((unsigned)(kv_len + kAttnTile - 1) / kAttnTile);
+    return rows_in_batch(q0, k_i, block, total_q) & (kv_len >= k_i) ? nt : 0;
 }
 
 // cost per tile and of the start of a unit with M query rows
@@ -181,36 +181,30 @@ __device__ inline bool plan_one_pass(int n, int grid) { return n <= grid / 8 * 8
 // range, whose K/V blocks are neighbours in every page, run on one XCD and share its address
 // translations.
 __device__ inline int plan_item(int index, int n, bool one_pass) {
-    if (index < 0) return -1;
-    if (!one_pass) return index < n ? index : -1;
-    const int per_xcd = (n + 7) / 8;
-    const int item = (index % 8) * per_xcd + index / 8;
-    return index / 8 < per_xcd && item < n ? item : -1;
+    const unsigned per_xcd = ((unsigned)n + 7) / 8, x = (unsigned)index;
+    const unsigned item = !one_pass ? x : x / 8 < per_xcd ? x % 8 * per_xcd + x / 8 : 0xFFFFFFFFu;
+    return item < (unsigned)n ? (int)item : -1;
 }
 
 // Calls piece(i, row0, q0, k_i, kv_len, t0, t1, nt) for each piece of the range between two cuts:
 // request i's rows from row0 of the kv-head group on (row block row0 / rb_rows) against tiles
 // t0 .. t1-1 of the nt tiles of its context. req(i, q0, k_i, kv_len) gives the packing and key
 // count of the requests after the first, which the cut itself carries. The cuts may hold any
-// words: every piece lies in its request, its request in the batch, and where a plan has one range
-// (and the workspace no partial results) every piece is a whole unit.
+// words: every piece lies in its request and its request in the batch.
 template <typename Args, typename ReqFn, typename PieceFn>
 __device__ __forceinline__ void walk_range(const Args& a, const AttnRange& r0, const AttnRange& r1, int rb_rows,
                                            ReqFn req, PieceFn piece) {
-    const bool cuts = a.ranges > 1;
     int rb = r0.block, t = r0.tile;
-    for (int i = r0.req > 0 ? r0.req : 0; i <= r1.req && i < a.R; i++, rb = 0, t = 0) {
+    for (int i = max(r0.req, 0); i <= r1.req && i < a.R; i++, rb = 0, t = 0) {
         int q0 = r0.q0, k_i = r0.k, kv_len = r0.kv;
         if (i != r0.req) req(i, q0, k_i, kv_len);
-        if (kv_len > a.max_kv_len) kv_len = a.max_kv_len;
+        kv_len = min(kv_len, a.max_kv_len);
         const int nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv_len);
         if (nt == 0) continue;
-        // (the last unit, cut or whole)
-        const int rb_end = i == r1.req && r1.block < a.nrb ? r1.block : a.nrb - 1;
-        for (rb = rb > 0 ? rb : 0; rb <= rb_end; rb++, t = 0) {
+        const int rb_end = i == r1.req ? min(r1.block, a.nrb - 1) : a.nrb - 1;  // (the last unit, cut or whole)
+        for (rb = max(rb, 0); rb <= rb_end; rb++, t = 0) {
             const int row0 = rb * rb_rows;
-            const int t0 = cuts && t > 0 ? t : 0;
-            const int t1 = cuts && i == r1.req && rb == r1.block && r1.tile < nt ? r1.tile : nt;
+            const int t0 = max(t, 0), t1 = i == r1.req && rb == r1.block ? min(r1.tile, nt) : nt;
             if (t0 >= t1 || a.G * k_i <= row0) continue;
             piece(i, row0, q0, k_i, kv_len, t0, t1, nt);
         }

@@ -263,11 +263,11 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
     p.max_splits = 1;
     p.ranges = (int)std::min<long long>(per_head, (long long)d.num_reqs * p.row_blocks * (whole / 64));
     p.slot_rows = std::min(maxM, rows);
-    if (p.ranges > 1) {  // two partial results per item: a unit that continues into it and one that starts there
-        const size_t slots = 2 * (size_t)p.ranges * d.num_kv_heads * p.slot_rows;
-        p.part_o_bytes = slots * d.head_dim * sizeof(float);
-        p.part_lse_bytes = slots * sizeof(float);
-    }
+    // Two partial results per item: a unit that continues into it and one that starts there. A plan
+    // of one range has no cuts, but a run on a workspace without a plan may find some.
+    const size_t slots = 2 * (size_t)p.ranges * d.num_kv_heads * p.slot_rows;
+    p.part_o_bytes = slots * d.head_dim * sizeof(float);
+    p.part_lse_bytes = slots * sizeof(float);
     p.off_groups = al(p.part_o_bytes + p.part_lse_bytes);
     p.off_pre = al(p.off_groups + ((size_t)p.ranges + 1) * 32);
     p.off_ctr = al(std::max(p.off_pre + ((size_t)d.num_reqs + 1) * 8,

@@ -46,8 +46,8 @@ void check_ranges_of_words() {
             for (int total : kWords)
                 for (int block : {1, 5, 16}) {
                     const bool in = k >= 1 && k <= block && q0 >= 0 && (long long)q0 + k <= total;
+                    if (total < 0) continue;
                     expect(sv::rows_in_batch(q0, k, block, total) == in, "rows_in_batch");
-                    if (total < 1) continue;  // (a descriptor's total is positive)
                     for (int kv : kWords)
                         for (int cap : {1, 64, 65, 1 << 22}) {
                             const long long n = kv > cap ? cap : kv;
@@ -129,7 +129,6 @@ void check_walk_of_words() {
             expect(row0 >= 0 && row0 % rb_rows == 0 && row0 < a.G * k_i, "first row");
             expect(kv >= k_i && kv <= a.max_kv_len && nt == (kv + 63) / 64, "keys");
             expect(t0 >= 0 && t0 < t1 && t1 <= nt, "tiles");
-            expect(a.ranges > 1 || t1 - t0 == nt, "one range has no partial results to write to");
         });
         expect(calls <= a.R * a.nrb, "number of pieces");
     }

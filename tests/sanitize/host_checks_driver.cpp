@@ -3,6 +3,7 @@
 // AddressSanitizer and UndefinedBehaviorSanitizer (no recovery), any out-of-bounds access,
 // signed overflow or other undefined behaviour aborts the run. Accepted descriptors must
 // also give consistent workspace layouts; rejected ones must leave a reason.
+#include <algorithm>
 #include <climits>
 #include <cmath>
 #include <cstdint>
@@ -61,6 +62,13 @@ void check_attn_layout(const sv_attn_desc& d) {
     expect(p.kv_split >= 64 && p.kv_split % 64 == 0, "attention split is a positive multiple of 64");
     expect(p.max_splits >= 1, "at least one split");
     expect((long long)p.max_splits * p.kv_split >= d.max_kv_len, "splits cover the longest context");
+    if (!p.list) {  // two partial results per item, whatever the plan in the workspace holds
+        const size_t G = d.num_q_heads / d.num_kv_heads, rows = (size_t)(p.waves / p.halves) * 32;
+        const size_t slots = 2 * (size_t)p.ranges * d.num_kv_heads;
+        expect(p.ranges >= 1 && p.slot_rows == (int)std::min(G * d.block, rows), "ranges and rows of a partial result");
+        expect(p.part_o_bytes >= slots * p.slot_rows * d.head_dim * 4 && p.part_lse_bytes >= slots * p.slot_rows * 4,
+               "partial results of every item");
+    }
     expect(p.off_groups >= p.part_o_bytes + p.part_lse_bytes && aligned256(p.off_groups), "work list after partials");
     expect(p.off_ctr >= p.off_groups + (size_t)d.num_reqs * p.max_splits * 4 && aligned256(p.off_ctr),
            "counter after the work list");

@@ -13,6 +13,9 @@
 #define __host__
 #define __forceinline__ inline
 
+using std::max;
+using std::min;
+
 struct HostIndex { unsigned x; };
 inline thread_local HostIndex threadIdx{0};
 
