@@ -25,7 +25,8 @@ SOURCES = ["sv_api.cpp", "sv_host.cpp", "budget.hip", "accept.hip", "attn.hip",
            "attn_list.hip", "pack.hip"]
 PROBE_SOURCES = ["read_probe.hip"]
 COMMON = ["--offload-arch=" + ARCH, "-O3", "-std=c++17", "-fPIC", "-I" + INC, "-I" + CSRC,
-          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function"]
+          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
+          "-Werror=align-mismatch"]  # a vector load must keep the alignment of the type it is made through
 
 
 def _compile(src: str, verbose: bool) -> str:

@@ -65,13 +65,6 @@ __device__ inline float to_f(uint16_t h) { return bf2f(h); }
 template <typename T>
 __device__ inline float load_x(const T* row, int v) { return to_f(row[v]); }
 
-// 16-byte load with the non-temporal hint, for rows streamed once per pass (the
-// statistics and argmax passes): they would only evict reused lines from the caches
-template <typename V>
-__device__ inline V stream_load(const V* p) {
-    return __builtin_nontemporal_load(p);
-}
-
 // fp32 probability of a token from its stored value x and its row's (max m, 1/sum): softmax(l / T)
 // in logits mode, 2^(l * (log2e / T) - m * log2e) * (1/sum) with one fused multiply-add before
 // the exponent; the stored value in probability mode. The draw's weights (residual_xy) compute
@@ -144,13 +137,21 @@ struct Vec {
     typedef type unaligned __attribute__((aligned(sizeof(T))));
 };
 
+// 16-byte load with the non-temporal hint, for rows streamed once per pass (the
+// statistics and argmax passes): they would only evict reused lines from the caches.
+// (T is named by the caller: deduced from the pointer, the vector would lose its alignment.)
+template <typename T>
+__device__ inline typename Vec<T>::type stream_load(const typename Vec<T>::unaligned* p) {
+    return __builtin_nontemporal_load(p);
+}
+
 // The N elements v0 .. v0+N-1 of a row clipped to [beg, end) with end - beg >= N: one load from
 // inside the range; elements outside it are left out by the caller (first: index of x[0]).
 template <typename T, bool STREAM>
 __device__ inline typename Vec<T>::type load_clipped(const T* row, int v0, int end, int& first) {
     first = min(v0, end - Vec<T>::N);
     const typename Vec<T>::unaligned* p = (const typename Vec<T>::unaligned*)(row + first);
-    return STREAM ? (typename Vec<T>::type)stream_load(p) : (typename Vec<T>::type)*p;
+    return STREAM ? stream_load<T>(p) : (typename Vec<T>::type)*p;
 }
 
 // (max, sum of 2^((x - max) log2e)) of x = l * invT over the chunk [beg, end) of one row,
@@ -168,7 +169,7 @@ __device__ __forceinline__ float2 chunk_stats(const T* row, int beg, int end, in
         const typename Vec<T>::unaligned* rv = (const typename Vec<T>::unaligned*)(row + beg);
         typename Vec<T>::type v[kStatsLoads];
 #pragma unroll
-        for (int k = 0; k < kStatsLoads; k++) v[k] = stream_load(rv + tid + k * kThreads);
+        for (int k = 0; k < kStatsLoads; k++) v[k] = stream_load<T>(rv + tid + k * kThreads);
 #pragma unroll
         for (int k = 0; k < kStatsLoads; k++)
 #pragma unroll
@@ -848,7 +849,7 @@ __global__ __launch_bounds__(kThreads) void argmax_kernel(AcceptArgs a) {
         const typename Vec<T>::unaligned* rv = (const typename Vec<T>::unaligned*)(row + beg);
         vec_t v[kStatsLoads];
 #pragma unroll
-        for (int k = 0; k < kStatsLoads; k++) v[k] = stream_load(rv + tid + k * kThreads);
+        for (int k = 0; k < kStatsLoads; k++) v[k] = stream_load<T>(rv + tid + k * kThreads);
 #pragma unroll
         for (int k = 0; k < kStatsLoads; k++)
 #pragma unroll

@@ -60,7 +60,7 @@ __device__ inline int plan_ranges(int stored, int most) { return stored < 0 ? 0 
 __device__ inline int plan_tiles(int block, int total_q, int max_kv_len, int q0, int k_i, int kv_len) {
     if (kv_len > max_kv_len) kv_len = max_kv_len;
     const int nt = (int)((unsigned)(kv_len + kAttnTile - 1) / kAttnTile);
-    return rows_in_batch(q0, k_i, block, total_q) & (kv_len >= k_i) ? nt : 0;
+    return (rows_in_batch(q0, k_i, block, total_q) & (kv_len >= k_i)) ? nt : 0;
 }
 
 // cost per tile and of the start of a unit with M query rows

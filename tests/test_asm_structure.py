@@ -119,3 +119,24 @@ def test_checker_flags_a_threaded_claim():
     lines = listing.split("\n")
     found = claims_and_barriers(lines, r"kernel")
     assert found == [("_ZN2sv6kernelEv", "BB2_130", "BB2_137")]
+
+
+def test_vector_loads_keep_their_alignment(tmp_path):
+    """Rows of odd vocabularies start at any element: the acceptance's 16-byte loads are made
+    through types of the element's alignment. A pointer to one passed on as a 16-byte aligned
+    vector is an error in the build, and the loads are single 16-byte instructions all the same."""
+    from paper_2607_25852_amd import build
+    assert "-Werror=align-mismatch" in build.COMMON
+    src = tmp_path / "planted.hip"
+    src.write_text("typedef float v4 __attribute__((ext_vector_type(4)));\n"
+                   "typedef v4 u4 __attribute__((aligned(4)));\n"
+                   "template <typename V> __device__ V get(const V* p) { return __builtin_nontemporal_load(p); }\n"
+                   "__global__ void k(const float* p, float* q) { q[0] = get((const u4*)(p + 1))[0]; }\n")
+    r = subprocess.run([HIPCC, "-x", "hip", *build.COMMON, "-fsyntax-only", str(src)], capture_output=True, text=True)
+    assert r.returncode != 0 and "align-mismatch" in r.stderr, r.stderr[-2000:]
+    r = subprocess.run([HIPCC, "-x", "hip", *build.COMMON, "-fsyntax-only", os.path.join(CSRC, "accept.hip")],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    for name, body in _functions(_assemble("accept.hip", tmp_path)):
+        if re.search(r"rowstats_kernel|argmax_kernel|dstats_chunk_kernel", name):
+            assert sum("global_load_dwordx4" in l and " nt" in l for l in body) >= 8, name
