@@ -37,7 +37,7 @@ namespace {
 struct RangeArgs : AttnArgs {
     int ranges, slot_rows;  // most ranges per head, rows of a partial result
 };
-static_assert(kPlanGrid == kAttnItems && sizeof(AttnRange) == 32, "the host sizes the plan");
+static_assert(kPlanGrid == kAttnItems && kPlanUnits == kAttnListUnits && sizeof(AttnRange) == 32, "the host sizes the plan");
 
 // ---------------------------------------------------------------------------------
 // bf16 MFMA kernel
@@ -607,13 +607,13 @@ __device__ __forceinline__ void attn_item(const RangeArgs& a, LdsRing<HD, NBUF>&
 
 // The plan (attn_plan.h), built by one workgroup.
 __global__ __launch_bounds__(1024) void attn_plan_kernel(RangeArgs a, AttnPlanArgs pa) {
-    __shared__ uint64_t pre[kPlanLdsReqs + 1];
-    __shared__ uint64_t wsum[1024 / 64];
+    __shared__ uint32_t pre[kPlanUnits];  // (R units at least)
+    __shared__ uint32_t wsum[1024 / 64];
     build_attn_plan<1024>(pa, [&](int i, int& q0, int& k_i, int& kv) {
         q0 = a.qo[i];
         k_i = a.qo[i + 1] - q0;
         kv = a.kv_lens[i];
-    }, a.R <= kPlanLdsReqs ? pre : pa.pre, wsum);
+    }, pre, wsum);
 }
 
 // Persistent kernel: a workgroup takes the item of its own index, then claims further ones
@@ -881,7 +881,7 @@ AttnPlanArgs attn_plan_args(const sv_attn_desc& d, const AttnPlan& p, void* ws) 
     return AttnPlanArgs{d.num_reqs, d.block, d.total_q_max, d.max_kv_len, d.num_q_heads / d.num_kv_heads,
                         p.row_blocks, (p.waves / p.halves) * 32, p.ranges,
                         d.num_kv_heads, (AttnRange*)(w + p.off_groups),
-                        (uint64_t*)(w + p.off_pre), (int32_t*)(w + p.off_ctr)};
+                        (int32_t*)(w + p.off_ctr)};
 }
 
 AttnListArgs attn_list_args(const sv_attn_desc& d, const AttnPlan& p, void* ws) {

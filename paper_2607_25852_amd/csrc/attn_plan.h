@@ -22,7 +22,7 @@ namespace sv {
 constexpr int kAttnTile = 64;       // KV tokens per tile of the attention kernel
 constexpr int kPlanMinTiles = 6;    // no range of the automatic plan is shorter
 constexpr int kPlanGrid = 256;      // compute units
-constexpr int kPlanLdsReqs = 2048;  // the plan kernel keeps the costs of more requests in the workspace
+constexpr int kPlanUnits = 2 * kPlanGrid;  // from this many units on the work is a list (attn_list.hip)
 constexpr int kPlanSnapTiles = 2;   // a cut this close to a unit's end is moved onto it
 // Cost of a unit, in sixteenths of the time of one tile of a unit of at most 64 query rows
 // (bound by its K/V stream): its start and end (descriptors, page ids, queries, the first
@@ -34,6 +34,8 @@ constexpr unsigned kCostStart = 100, kCostStart65 = 144, kCostTile = 16, kCostTi
 // (attention over 188 MB to 6.4 GB, several cards), so their ranges are this many 1024ths
 // shorter and the others' longer.
 constexpr unsigned kOddXcd = 17;
+static_assert(kPlanUnits * (kCostStart65 + (uint64_t)kCostWideTile * ((1 << 22) / kAttnTile)) < 1u << 31,
+              "the cost of a line, and a step more, fit 32 bits");
 
 // one cut of the line: the range starts at this tile of this unit. The request's packing and
 // key count go with it, which saves the readers a dependent load.
@@ -48,7 +50,6 @@ struct AttnPlanArgs {
     int ranges;        // most ranges per head the workspace holds
     int heads;         // kv-heads
     AttnRange* recs;   // [ranges + 1]
-    uint64_t* pre;     // [R + 1] cost before each request, used above kPlanLdsReqs requests
     int32_t* ctr;      // {ranges per head, claim counter, finished workgroups}
 };
 
@@ -76,61 +77,54 @@ __device__ inline unsigned plan_head_cost(const AttnPlanArgs& a, int k_i, int nt
     return c;
 }
 
-// NT threads of one workgroup. pre: R + 1 entries in LDS (or a.pre); wsum: NT / 64 entries of
-// LDS. req(i, q0, k_i, kv_len) gives request i's packing and key count. The caller's kernel
-// end publishes the plan.
+// NT threads of one workgroup. pre: R + 1 entries of LDS, wsum: NT / 64 entries of LDS.
+// req(i, q0, k_i, kv_len) gives request i's packing and key count. The caller's kernel end
+// publishes the plan. Costs are 32 bits: ranges are for fewer than kPlanUnits units, each of at
+// most 2^16 tiles.
 template <int NT, typename ReqFn>
-__device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint64_t* pre, uint64_t* wsum) {
+__device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint32_t* pre, uint32_t* wsum) {
     static_assert(NT % 64 == 0, "plan threads");
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    auto head_cost = [&](int i, int& k_i, int& nt) {
-        int q0, kv;
-        req(i, q0, k_i, kv);
-        nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv);
-        return plan_head_cost(a, k_i, nt);
-    };
-    // 1. cost before each request: thread t takes requests t*per .. t*per + per - 1
-    const int per = (a.R + NT - 1) / NT;
-    uint64_t loc = 0;
-    for (int e = 0; e < per; e++) {
-        const int i = tid * per + e;
-        int k_i, nt;
-        if (i < a.R) loc += head_cost(i, k_i, nt);
+    // 1. cost before each request, one request per thread at a time
+    uint32_t W = 0;  // the cost of the line so far
+    for (int i0 = 0; i0 < a.R; i0 += NT) {
+        const int i = i0 + tid;
+        uint32_t cost = 0;
+        if (i < a.R) {
+            int q0, k_i, kv;
+            req(i, q0, k_i, kv);
+            cost = plan_head_cost(a, k_i, plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv));
+        }
+        uint32_t incl = cost;
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t v = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += v;
+        }
+        uint32_t before = W;
+        if constexpr (NT == 64) {
+            W += __shfl(incl, 63, 64);
+        } else {
+            if (lane == 63) wsum[w] = incl;
+            __syncthreads();
+            for (int k = 0; k < NT / 64; k++) {
+                if (k < w) before += wsum[k];
+                W += wsum[k];
+            }
+            __syncthreads();  // (the sums of the next requests go to the same place)
+        }
+        if (i < a.R) pre[i] = before + incl - cost;
     }
-    uint64_t incl = loc;
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint64_t v = __shfl_up(incl, off, 64);
-        if (lane >= off) incl += v;
-    }
-    if (lane == 63) wsum[w] = incl;
-    __syncthreads();
-    uint64_t base = incl - loc, W = 0;
-    for (int k = 0; k < NT / 64; k++) {
-        if (k < w) base += wsum[k];
-        W += wsum[k];
-    }
-    for (int e = 0; e < per; e++) {
-        const int i = tid * per + e;
-        if (i > a.R) break;
-        pre[i] = base;
-        int k_i, nt;
-        if (i < a.R) base += head_cost(i, k_i, nt);
-    }
-    if (tid == 0) pre[a.R] = W;
     __syncthreads();
     // 2. the size of the ranges
-    const uint64_t least = kCostStart + kPlanMinTiles * kCostTile;
-    const uint64_t up = W + (unsigned)a.ranges - 1;
-    uint64_t step = up >> 32 ? up / (unsigned)a.ranges : (unsigned)up / (unsigned)a.ranges;
-    if (step < least) step = least;
-    const uint64_t upto = W + step - 1;
-    const uint64_t want = upto >> 32 || step >> 32 ? upto / step : (unsigned)upto / (unsigned)step;
-    const int n = want < (uint64_t)a.ranges ? (int)want : a.ranges;
+    constexpr uint32_t least = kCostStart + kPlanMinTiles * kCostTile;
+    const uint32_t even = (W + (uint32_t)a.ranges - 1) / (uint32_t)a.ranges;
+    const uint32_t step = even < least ? least : even;
+    const int n = (int)((W + step - 1) / step);  // (at most a.ranges)
     // the items of a range share an XCD when its workgroups hold whole ranges (attn.hip)
-    const bool skewed = n % 8 == 0 && n * a.heads <= kPlanGrid;
+    const bool skewed = n > 0 && n % 8 == 0 && n * a.heads <= kPlanGrid;
     // 3. the cuts: the request by binary search over the costs, then row block and tile
     for (int r = tid; r <= n; r += NT) {
-        uint64_t at = (uint64_t)r * step;
+        uint32_t at = (uint32_t)r * step;
         if (skewed) {  // (per XCD the ranges' sizes sum to per * step on average over two XCDs)
             const unsigned per = (unsigned)n / 8, x = (unsigned)r / per, k = (unsigned)r % per;
             at += (x & 1 ? per - k : k) * (step * kOddXcd / 1024);
@@ -146,7 +140,7 @@ __device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint64_
             int q0, k_i, kv;
             req(lo, q0, k_i, kv);
             const int nt = plan_tiles(a.block, a.total_q, a.max_kv_len, q0, k_i, kv);
-            unsigned x = (unsigned)(at - pre[lo]);
+            unsigned x = at - pre[lo];
             int rb = 0;
             unsigned uc = plan_unit_cost(a.G * k_i, nt);
             while (x >= uc && rb + 1 < a.nrb) {

@@ -278,8 +278,9 @@ __global__ __launch_bounds__(NT) void budget_kernel(BudgetArgs a, const float* _
         if (!pr.plan) return;
         __syncthreads();
         // 8. the verify-attention work plan over those key counts
-        // (ranges: the costs before each request go to the second key buffer: R <= NPAD, and the
-        // packing offsets fill at most half of the first)
+        // (list: its cursors follow the packing offsets in the key buffers, or the counts with one
+        // wave; ranges: the costs before each request follow the packing offsets, R + 1 words each
+        // in 4 * NPAD words of key buffers)
         auto req = [&](int i, int& q0, int& k_i, int& kv) {
             q0 = qs[i];
             k_i = qs[i + 1] - q0;
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(NT) void budget_kernel(BudgetArgs a, const float* _
         if constexpr (std::is_same_v<Plan, AttnListArgs>)
             build_attn_list<NT>(pr.pa, req, NT == kThreads ? qs + ((R + 1 + 63) & ~63) : cnt + kSmallMax, scan_tmp);
         else
-            build_attn_plan<NT>(pr.pa, req, &lds[0][0] + (R + 2) / 2, wtot);
+            build_attn_plan<NT>(pr.pa, req, (uint32_t*)qs + R + 1, (uint32_t*)scan_tmp);
     }
 }
 

@@ -217,7 +217,7 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
     // A split size given by the caller, and two units per compute unit or more: a work list
     // (attn_list.hip, with what either side measured). Its splits are each request's own, so that
     // with a given size a request's results do not depend on the rest of the batch.
-    if (d.kv_split > 0 || (long long)d.num_reqs * d.num_kv_heads * p.row_blocks >= 2 * kAttnItems) {
+    if (d.kv_split > 0 || (long long)d.num_reqs * d.num_kv_heads * p.row_blocks >= kAttnListUnits) {
         p.list = true;
         int split = d.kv_split;
         if (split <= 0) {
@@ -269,9 +269,7 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
     p.part_o_bytes = slots * d.head_dim * sizeof(float);
     p.part_lse_bytes = slots * sizeof(float);
     p.off_groups = al(p.part_o_bytes + p.part_lse_bytes);
-    p.off_pre = al(p.off_groups + ((size_t)p.ranges + 1) * 32);
-    p.off_ctr = al(std::max(p.off_pre + ((size_t)d.num_reqs + 1) * 8,
-                            p.off_groups + (size_t)d.num_reqs * p.max_splits * sizeof(int32_t)));
+    p.off_ctr = al(p.off_groups + ((size_t)p.ranges + 1) * 32);  // the cuts
     p.ws_bytes = p.off_ctr + 3 * sizeof(int32_t);
     return p;
 }

@@ -27,6 +27,7 @@ struct ReqPlan {
 
 // ---- workspace layouts --------------------------------------------------------------
 constexpr int kAttnItems = 256;  // items of the automatic attention plan: one per compute unit
+constexpr int kAttnListUnits = 2 * kAttnItems;  // (request, kv-head, row block) units that take the list
 struct AttnPlan {
     bool list;        // a list of items (many units or a given split, attn_list.hip), else ranges of equal cost (attn.hip)
     int kv_split;     // list: tokens per work item, the caller's or chosen; ranges: the longest context
@@ -39,7 +40,6 @@ struct AttnPlan {
     size_t part_o_bytes;    // partial outputs (fp32), offset 0
     size_t part_lse_bytes;  // partial log-sum-exps, after part_o
     size_t off_groups;      // the list or the ranges of the plan
-    size_t off_pre;         // cost before each request (plans of many requests)
     size_t off_ctr;         // {items or ranges, claim counter, finished workgroups}
     size_t ws_bytes;        // total workspace (0 for the fp32 path)
 };

@@ -135,6 +135,152 @@ void check_walk_of_words() {
     expect(pieces > 10000, "the words gave pieces");
 }
 
+// ---- whole plans: the cuts of 64-bit arithmetic, every tile once, every partial result merged ----
+struct Round {
+    sv::AttnPlanArgs a{};
+    std::vector<int> q0, k, kv;
+};
+
+uint64_t unit_cost(int M, int nt) {
+    if (M <= 0 || nt <= 0) return 0;
+    return (M > 64 ? 144 : 100) + (uint64_t)nt * (M > 128 ? 32 : M > 64 ? 20 : 16);
+}
+
+int tiles_of(const Round& r, int i) {
+    const int kv = std::min(r.kv[i], r.a.max_kv_len);
+    const bool ok = r.k[i] >= 1 && r.k[i] <= r.a.block && r.q0[i] >= 0 && (long long)r.q0[i] + r.k[i] <= r.a.total_q;
+    return ok && kv >= r.k[i] ? (kv + 63) / 64 : 0;
+}
+
+// the cuts by their definition: cut c at c equal parts of the line's cost (with the odd XCDs'
+// parts 17/1024 shorter where the ranges are shared out evenly), moved onto a unit's end within
+// two tiles of it
+std::vector<sv::AttnRange> cuts_of(const Round& r) {
+    const sv::AttnPlanArgs& a = r.a;
+    uint64_t W = 0;
+    std::vector<uint64_t> before;
+    for (int i = 0; i < a.R; i++) {
+        before.push_back(W);
+        for (int rb = 0; rb < a.nrb; rb++) W += unit_cost(a.G * r.k[i] - rb * a.rb_rows, tiles_of(r, i));
+    }
+    const uint64_t step = std::max<uint64_t>((W + a.ranges - 1) / a.ranges, 100 + 6 * 16);
+    const int n = (int)((W + step - 1) / step);
+    std::vector<sv::AttnRange> out(n + 1, sv::AttnRange{a.R, 0, 0, 0, 0, 0, 0, 0});
+    for (int c = 0; c < n; c++) {
+        uint64_t at = c * step;
+        if (n % 8 == 0 && n * a.heads <= 256) {
+            const int per = n / 8, x = c / per, part = c % per;
+            at += (uint64_t)(x % 2 ? per - part : part) * (step * 17 / 1024);
+        }
+        if (at >= W) continue;
+        int i = 0;
+        while (i + 1 < a.R && before[i + 1] <= at) i++;
+        uint64_t x = at - before[i];
+        const int nt = tiles_of(r, i);
+        int rb = 0;
+        while (rb + 1 < a.nrb && x >= unit_cost(a.G * r.k[i] - rb * a.rb_rows, nt))
+            x -= unit_cost(a.G * r.k[i] - rb++ * a.rb_rows, nt);
+        const int M = a.G * r.k[i] - rb * a.rb_rows;
+        const uint64_t start = M > 64 ? 144 : 100;
+        int t = x > start ? (int)((x - start) / (M > 128 ? 32 : M > 64 ? 20 : 16)) : 0;
+        if (t <= 2) t = 0;
+        if (t >= nt || (t > 0 && nt - t <= 2)) t = 0, rb++;
+        out[c] = sv::AttnRange{i, rb, t, r.q0[i], r.k[i], r.kv[i], 0, 0};
+    }
+    return out;
+}
+
+template <int NT>
+void check_plan(Round& r) {
+    sv::AttnPlanArgs& a = r.a;
+    std::vector<sv::AttnRange> recs(a.ranges + 1);
+    int32_t ctr[3] = {-7, -7, -7};
+    a.recs = recs.data();
+    a.ctr = ctr;
+    std::vector<uint32_t> pre(a.R + 1), wsum(NT / 64);
+    hosthip::run_workgroup(NT, [&] {
+        sv::build_attn_plan<NT>(a, [&](int i, int& q0, int& k, int& kv) {
+            q0 = r.q0[i];
+            k = r.k[i];
+            kv = r.kv[i];
+        }, pre.data(), wsum.data());
+    });
+    const std::vector<sv::AttnRange> want = cuts_of(r);
+    const int n = ctr[0];
+    expect(n == (int)want.size() - 1 && n <= a.ranges && ctr[1] == 0 && ctr[2] == 0, "the counts of a plan");
+    for (int c = 0; c <= n; c++)
+        expect(recs[c].req == want[c].req && recs[c].block == want[c].block && recs[c].tile == want[c].tile &&
+                   recs[c].q0 == want[c].q0 && recs[c].k == want[c].k && recs[c].kv == want[c].kv, "the cuts");
+    // the walk: per unit, its pieces in order
+    std::vector<int> next(a.R * a.nrb, 0);
+    std::vector<int> cut_slot(2 * a.ranges, -1);  // the unit whose piece a partial result holds
+    for (int c = 0; c < n; c++)
+        sv::walk_range(a, recs[c], recs[c + 1], a.rb_rows, [&](int i, int& q0, int& k, int& kv) {
+            q0 = r.q0[i];
+            k = r.k[i];
+            kv = r.kv[i];
+        }, [&](int i, int row0, int q0, int k, int, int t0, int t1, int nt) {
+            const int unit = i * a.nrb + row0 / a.rb_rows;
+            expect(q0 == r.q0[i] && k == r.k[i] && nt == tiles_of(r, i), "a piece's request");
+            expect(t0 == next[unit], "the tiles of a unit follow each other");
+            next[unit] = t1;
+            if (t1 - t0 == nt) return;
+            const int slot = 2 * c + (t0 == 0);
+            expect(cut_slot[slot] == -1, "one piece per partial result");
+            cut_slot[slot] = unit;
+        });
+    for (int i = 0; i < a.R; i++)
+        for (int rb = 0; rb < a.nrb; rb++)
+            expect(next[i * a.nrb + rb] == (a.G * r.k[i] > rb * a.rb_rows ? tiles_of(r, i) : 0), "every tile once");
+    // the merge: from the first cut inside a unit on, the piece that starts it and one per cut
+    for (int c = 1; c < n; c++) {
+        if (recs[c].tile <= 0) continue;
+        const int unit = recs[c].req * a.nrb + recs[c].block;
+        const bool first = recs[c - 1].tile <= 0 || recs[c - 1].req * a.nrb + recs[c - 1].block != unit;
+        if (!first) continue;
+        expect(cut_slot[2 * (c - 1) + 1] == unit, "the start of a cut unit");
+        cut_slot[2 * (c - 1) + 1] = -1;
+        for (int s = c; s < n && recs[s].req == recs[c].req && recs[s].block == recs[c].block; s++) {
+            expect(cut_slot[2 * s] == unit, "the further pieces of a cut unit");
+            cut_slot[2 * s] = -1;
+        }
+    }
+    for (int slot : cut_slot) expect(slot == -1, "every partial result is merged");
+}
+
+void check_plans() {
+    const int kHeads[] = {1, 2, 3, 4, 7, 8, 16, 24, 100, 200};
+    for (int it = 0; it < 150; it++) {
+        Round r;
+        sv::AttnPlanArgs& a = r.a;
+        a.heads = kHeads[below(10)];
+        a.G = 1 << below(7);
+        a.block = 1 + below(16);
+        const bool wide = a.G * a.block > 128;
+        a.rb_rows = wide ? 256 : 128;
+        a.nrb = (a.G * a.block + a.rb_rows - 1) / a.rb_rows;
+        const int most = std::max(1, 511 / (a.heads * a.nrb));
+        a.R = it % 5 ? 1 + below(most) : most;
+        a.max_kv_len = it % 7 == 0 ? 1 << 22 : 1 << (1 + below(18));
+        int per_head = a.heads <= 256 ? 256 / a.heads : 0;
+        if (per_head * a.heads * 10 < 256 * 9) per_head = (4 * 256 + a.heads - 1) / a.heads;
+        a.ranges = (int)std::min<long long>(per_head, (long long)a.R * a.nrb * ((a.max_kv_len + 63) / 64));
+        int q = 0;
+        for (int i = 0; i < a.R; i++) {
+            r.q0.push_back(q);
+            r.k.push_back(1 + below(a.block));
+            const int top = it % 3 ? a.max_kv_len : 1 << below(23);  // (longer contexts are cut to the longest)
+            r.kv.push_back(it % 7 == 0 ? a.max_kv_len : r.k[i] + below(top));
+            if (it % 11 == 0 && i % 3 == 1) r.k[i] = word(a.block) % 1000000;  // malformed
+            if (it % 13 == 0 && i % 4 == 2) r.kv[i] = word(a.max_kv_len);
+            q += std::max(0, std::min(r.k[i], a.block));
+        }
+        a.total_q = std::max(1, it % 17 ? q : q - 2);
+        if (it % 25) check_plan<64>(r);
+        else check_plan<512>(r);
+    }
+}
+
 }  // namespace
 
 int main() {
@@ -142,6 +288,7 @@ int main() {
     check_item_counts();
     check_items_of_grids();
     check_walk_of_words();
+    check_plans();
     std::printf("ok\n");
     return 0;
 }

@@ -70,8 +70,8 @@ void check_attn_layout(const sv_attn_desc& d) {
                "partial results of every item");
     }
     expect(p.off_groups >= p.part_o_bytes + p.part_lse_bytes && aligned256(p.off_groups), "work list after partials");
-    expect(p.off_ctr >= p.off_groups + (size_t)d.num_reqs * p.max_splits * 4 && aligned256(p.off_ctr),
-           "counter after the work list");
+    const size_t plan = p.list ? (size_t)d.num_reqs * p.max_splits * 4 : ((size_t)p.ranges + 1) * 32;
+    expect(p.off_ctr >= p.off_groups + plan && aligned256(p.off_ctr), "counters after the list or the cuts");
     expect(p.ws_bytes >= p.off_ctr + 8, "workspace holds the counters");
 }
 
