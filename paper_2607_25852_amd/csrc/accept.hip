@@ -147,11 +147,10 @@ __device__ inline typename Vec<T>::type stream_load(const typename Vec<T>::unali
 
 // The N elements v0 .. v0+N-1 of a row clipped to [beg, end) with end - beg >= N: one load from
 // inside the range; elements outside it are left out by the caller (first: index of x[0]).
-template <typename T, bool STREAM>
+template <typename T>
 __device__ inline typename Vec<T>::type load_clipped(const T* row, int v0, int end, int& first) {
     first = min(v0, end - Vec<T>::N);
-    const typename Vec<T>::unaligned* p = (const typename Vec<T>::unaligned*)(row + first);
-    return STREAM ? stream_load<T>(p) : (typename Vec<T>::type)*p;
+    return stream_load<T>((const typename Vec<T>::unaligned*)(row + first));
 }
 
 // (max, sum of 2^((x - max) log2e)) of x = l * invT over the chunk [beg, end) of one row,
@@ -179,7 +178,7 @@ __device__ __forceinline__ float2 chunk_stats(const T* row, int beg, int end, in
         for (int k = 0; k < kStatsLoads; k++) {
             const int v0 = beg + (tid + k * kThreads) * N;
             int first;
-            const typename Vec<T>::type v = load_clipped<T, true>(row, v0, end, first);
+            const typename Vec<T>::type v = load_clipped<T>(row, v0, end, first);
 #pragma unroll
             for (int e = 0; e < N; e++) x[k * N + e] = first + e >= v0 ? to_f(v[e]) * invT : -INFINITY;
         }
@@ -865,7 +864,7 @@ __global__ __launch_bounds__(kThreads) void argmax_kernel(AcceptArgs a) {
         int first[kStatsLoads];
 #pragma unroll
         for (int k = 0; k < kStatsLoads; k++)
-            v[k] = load_clipped<T, true>(row, beg + (tid + k * kThreads) * VEC, end, first[k]);
+            v[k] = load_clipped<T>(row, beg + (tid + k * kThreads) * VEC, end, first[k]);
 #pragma unroll
         for (int k = 0; k < kStatsLoads; k++)
 #pragma unroll

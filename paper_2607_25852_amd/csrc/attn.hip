@@ -673,7 +673,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16_kernel(RangeArgs a, cons
 // first cut inside a unit merge its pieces: the one that starts it (the range before the cut)
 // and one per cut. One thread per (query row, 4-dim slice); up to 8 pieces' lse and partials
 // are loaded before any math.
-template <int HD, bool BF16OUT>
+template <int HD>
 __global__ __launch_bounds__(256) void attn_merge_kernel(RangeArgs a, const AttnRange* __restrict__ recs,
                                                          const int32_t* __restrict__ ctr, int rb_rows) {
     constexpr int SL = HD / 4;  // 4-dim slices per row
@@ -731,14 +731,10 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(RangeArgs a, const Attn
         mx = bm;
     }
     const float inv = wsum > 0.0f ? 1.0f / wsum : 0.0f;
-    if (BF16OUT) {
-        uint64_t pk = 0;
+    uint64_t pk = 0;
 #pragma unroll
-        for (int e = 0; e < 4; e++) pk |= (uint64_t)f2bf(acc[e] * inv) << (16 * e);
-        *(uint64_t*)((uint16_t*)a.out + orow * HD + sl * 4) = pk;
-    } else {
-        *(f32x4*)((float*)a.out + orow * HD + sl * 4) = acc * inv;
-    }
+    for (int e = 0; e < 4; e++) pk |= (uint64_t)f2bf(acc[e] * inv) << (16 * e);
+    *(uint64_t*)((uint16_t*)a.out + orow * HD + sl * 4) = pk;
     if (a.lse && sl == 0) a.lse[orow] = wsum > 0.0f ? (mx + __log2f(wsum)) * kLn2 : -INFINITY;
 }
 
@@ -974,9 +970,9 @@ hipError_t launch_attn(const sv_attn_desc& d, const AttnPlan& plan, const void* 
     if (e != hipSuccess || plan.ranges <= 1) return e;
     const dim3 mgrid((plan.slot_rows * (d.head_dim / 4) + 255) / 256, d.num_kv_heads, plan.ranges - 1);
     if (d.head_dim == 128)
-        hipLaunchKernelGGL((attn_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows);
+        hipLaunchKernelGGL((attn_merge_kernel<128>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows);
     else
-        hipLaunchKernelGGL((attn_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows);
+        hipLaunchKernelGGL((attn_merge_kernel<64>), mgrid, dim3(256), 0, stream, a, pa.recs, ctr, pa.rb_rows);
     return hipGetLastError();
 }
 

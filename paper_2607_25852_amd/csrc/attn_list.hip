@@ -284,7 +284,6 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
             // and output lane jl receives dim 32t + 16(g%2) + jl of tokens 16c + 8q + 4(g/2) +
             // 0..3. The operands are read VPD MFMAs ahead; the first VPD are in flight while the
             // exponents of the first half are computed.
-            const int g = lane >> 4, jl = lane & 15;
             constexpr int NJ = 2 * DT;    // PV MFMAs per 32-token half
             constexpr int NT = NSB * NJ;  // PV MFMAs per tile for this wave
             constexpr int VPD = 4;
@@ -347,7 +346,6 @@ __device__ __forceinline__ void attn_item(const AttnArgs& a, LdsRing<HD, NBUF>& 
             l_run += ps0 + ps1;
         } else {
             // Half-tile waves: one online-softmax step per tile on the wave's half.
-            const int g = lane >> 4, jl = lane & 15;
             const int hh = th;
             const int tb_h = tb + hh * 32;
             if (tb_h + 31 > L || tb_h + 32 > tok_end) {
@@ -563,7 +561,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_list_kernel(AttnArgs a, const
 // the group, 4-dim slice); every split's lse and partial are loaded before any math (one
 // round of loads for up to 8 splits). Requests with a single split were written
 // directly by the main kernel and exit here.
-template <int HD, bool BF16OUT>
+template <int HD>
 __global__ __launch_bounds__(256) void attn_list_merge_kernel(AttnArgs a) {
     constexpr int SL = HD / 4;  // 4-dim slices per row
     const int h = blockIdx.y, i = blockIdx.z;
@@ -605,14 +603,10 @@ __global__ __launch_bounds__(256) void attn_list_merge_kernel(AttnArgs a) {
         mx = bm;
     }
     const float inv = wsum > 0.0f ? 1.0f / wsum : 0.0f;
-    if (BF16OUT) {
-        uint64_t pk = 0;
+    uint64_t pk = 0;
 #pragma unroll
-        for (int e = 0; e < 4; e++) pk |= (uint64_t)f2bf(acc[e] * inv) << (16 * e);
-        *(uint64_t*)((uint16_t*)a.out + orow * HD + sl * 4) = pk;
-    } else {
-        *(f32x4*)((float*)a.out + orow * HD + sl * 4) = acc * inv;
-    }
+    for (int e = 0; e < 4; e++) pk |= (uint64_t)f2bf(acc[e] * inv) << (16 * e);
+    *(uint64_t*)((uint16_t*)a.out + orow * HD + sl * 4) = pk;
     if (a.lse && sl == 0) a.lse[orow] = wsum > 0.0f ? (mx + __log2f(wsum)) * kLn2 : -INFINITY;
 }
 
@@ -649,9 +643,9 @@ hipError_t launch_attn_list(const AttnArgs& a, const AttnPlan& plan, int head_di
     if (e != hipSuccess || plan.max_splits <= 1) return e;
     const dim3 mgrid((a.G * a.block * (head_dim / 4) + 255) / 256, a.Hkv, a.R);
     if (head_dim == 128)
-        hipLaunchKernelGGL((attn_list_merge_kernel<128, true>), mgrid, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((attn_list_merge_kernel<128>), mgrid, dim3(256), 0, stream, a);
     else
-        hipLaunchKernelGGL((attn_list_merge_kernel<64, true>), mgrid, dim3(256), 0, stream, a);
+        hipLaunchKernelGGL((attn_list_merge_kernel<64>), mgrid, dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 

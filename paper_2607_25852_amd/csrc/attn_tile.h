@@ -46,8 +46,6 @@ struct AttnArgs {
     float scale;       // sm_scale
 };
 
-__device__ inline float bf2f(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
-
 // round-to-nearest-even fp32 -> bf16 bits
 __device__ inline uint16_t f2bf(float f) {
     uint32_t u = __float_as_uint(f);
@@ -87,7 +85,6 @@ __device__ inline void wait_vm() {
 }
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
-typedef int i32x4 __attribute__((ext_vector_type(4)));
 typedef short i16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 

@@ -20,7 +20,6 @@ namespace {
 constexpr int kThreads = 512;  // the workgroup of large rounds
 constexpr int kWave = 64;      // the workgroup of small rounds: one wave
 constexpr int kSmallMax = 128; // small rounds: R*b <= 128 (up to two keys per lane)
-constexpr int kMaxKeys = SV_MAX_BUDGET_POSITIONS;
 constexpr int kMaxReqs = SV_MAX_BUDGET_REQS;
 
 struct BudgetArgs {
