@@ -99,6 +99,21 @@ def test_attention_claim_and_barrier_share_a_loop(tmp_path):
         assert claim_loop is not None and claim_loop == barrier_loop, (name, claim_loop, barrier_loop)
 
 
+def test_list_claim_and_barrier_share_a_loop(tmp_path):
+    """The same for the work list's kernels, which always claim: four shapes of tile and page,
+    each with and without whole-tile waves."""
+    found = claims_and_barriers(_assemble("attn_list.hip", tmp_path), r"attn_list_kernel")
+    assert len({name for name, _, _ in found}) == 8, found
+    for name, claim_loop, barrier_loop in found:
+        assert claim_loop is not None and claim_loop == barrier_loop, (name, claim_loop, barrier_loop)
+
+
+def test_no_other_file_claims_work(tmp_path):
+    """The two tests above name every source whose kernels loop over claimed items."""
+    loops = [f for f in sorted(os.listdir(CSRC)) if f.endswith(".hip") and "atomicAdd(&ctr[" in open(os.path.join(CSRC, f)).read()]
+    assert loops == ["attn.hip", "attn_list.hip"], loops
+
+
 def test_checker_flags_a_threaded_claim():
     """The checker on a hand-written listing with the miscompiled shape: the claim in the
     outer loop, its barrier in an inner loop entered from the unit's latch."""
