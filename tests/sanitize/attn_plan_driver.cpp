@@ -281,9 +281,63 @@ void check_plans() {
     }
 }
 
+// ---- a run on the words of stdin: R block total_q max_kv_len G nrb heads ranges, qo, kv_lens, the
+// count and the cuts; prints the number of pieces and of merged units ----
+void check_run_on_words() {
+    auto in = [] {
+        int v = 0;
+        expect(std::scanf("%d", &v) == 1, "a word on stdin");
+        return v;
+    };
+    Shape a{};
+    a.R = in();
+    a.block = in();
+    a.total_q = in();
+    a.max_kv_len = in();
+    a.G = in();
+    a.nrb = in();
+    const int heads = in();
+    a.ranges = in();
+    const int rb_rows = a.G * a.block > 128 ? 256 : 128;
+    const int slot_rows = std::min(a.G * a.block, rb_rows);
+    std::vector<int> qo(a.R + 1), kv(a.R);
+    for (int& v : qo) v = in();
+    for (int& v : kv) v = in();
+    const int n = sv::plan_ranges(in(), a.ranges) * heads;
+    std::vector<sv::AttnRange> recs(a.ranges + 1);
+    for (auto& r : recs)
+        for (int* w : {&r.req, &r.block, &r.tile, &r.q0, &r.k, &r.kv, &r.pad0, &r.pad1}) *w = in();
+    std::vector<char> slots(2 * (size_t)a.ranges * heads * slot_rows);  // the rows of the partial results
+    long pieces = 0;
+    const bool one_pass = sv::plan_one_pass(n, 256);
+    for (int index = 0; index < (one_pass ? 256 : n + 256); index++) {
+        const int item = sv::plan_item(index, n, one_pass);
+        if (item < 0) continue;
+        const int rng = item / heads, h = item % heads;
+        sv::walk_range(a, recs.at(rng), recs.at(rng + 1), rb_rows, [&](int i, int& q0, int& k, int& kv_len) {
+            q0 = qo.at(i);
+            k = qo.at(i + 1) - q0;
+            kv_len = kv.at(i);
+        }, [&](int i, int row0, int q0, int k, int kv_len, int t0, int t1, int nt) {
+            pieces++;
+            expect(i >= 0 && i < a.R && row0 >= 0 && row0 < a.G * k, "a piece's request and rows");
+            expect(q0 >= 0 && k >= 1 && k <= a.block && (long long)q0 + k <= a.total_q, "rows of the batch");
+            expect(kv_len >= k && kv_len <= a.max_kv_len && 0 <= t0 && t0 < t1 && t1 <= nt, "tiles");
+            if (t1 - t0 == nt) return;
+            const size_t slot = 2 * ((size_t)rng * heads + h) + (t0 == 0);
+            for (int r = 0; r < std::min(a.G * k - row0, rb_rows); r++) slots.at(slot * slot_rows + r) = 1;
+        });
+    }
+    std::printf("ok %ld\n", pieces);
+}
+
 }  // namespace
 
-int main() {
+int main(int argc, char**) {
+    if (argc > 1) {
+        check_run_on_words();
+        return 0;
+    }
     check_ranges_of_words();
     check_item_counts();
     check_items_of_grids();

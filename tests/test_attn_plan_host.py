@@ -8,21 +8,48 @@ import subprocess
 
 import pytest
 
-from test_sanitizers import ROOT, SAN, _have, _run
+import attn_words
+from test_sanitizers import ENV_SAN, ROOT, SAN, _have, _run
 
 pytestmark = pytest.mark.skipif(not _have("g++"), reason="g++ not found")
 
 
-def test_plan_code_on_the_host(tmp_path):
-    exe = tmp_path / "attn_plan_driver"
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = tmp_path_factory.mktemp("attn_plan") / "attn_plan_driver"
     san = os.path.join(ROOT, "tests", "sanitize")
     subprocess.run(["g++", "-std=c++17", "-Wall", "-Wextra", "-Werror", *SAN, "-pthread",
                     "-I", os.path.join(san, "host_hip"), "-I", os.path.join(ROOT, "include"),
                     "-I", os.path.join(ROOT, "paper_2607_25852_amd", "csrc"),
                     os.path.join(san, "attn_plan_driver.cpp"), "-o", str(exe)], check=True)
-    r = _run([str(exe)])
+    return str(exe)
+
+
+def test_plan_code_on_the_host(driver):
+    r = _run([driver])
     assert r.returncode == 0, r.stdout[-1000:] + r.stderr[-4000:]
     assert r.stdout.startswith("ok"), r.stdout
+
+
+@pytest.mark.parametrize("shape", attn_words.SHAPES)
+def test_run_on_words_stays_in_bounds(driver, shape):
+    """The words that the GPU test of runs without a plan puts into the workspace: every piece they
+    make lies in the batch, its request and the partial results."""
+    Hq, Hkv, d, page, b, ctx = shape
+    _, qo, kv = attn_words.case(shape)
+    R, G, top = len(ctx), Hq // Hkv, int(kv.max())
+    ranges = attn_words.ranges_of(Hq, Hkv, b, R, top)
+    blocks = -(-G * b // (256 if G * b > 128 else 128))
+    pieces = {}
+    for kind in attn_words.KINDS:
+        count, rec = attn_words.words(kind, ranges, R, b, qo, kv)
+        nums = [R, b, int(qo[-1]), top, G, blocks, Hkv, ranges, *qo, *kv, count, *rec.ravel()]
+        r = subprocess.run([driver, "words"], input=" ".join(str(int(v)) for v in nums), capture_output=True, text=True,
+                           env=dict(os.environ, **ENV_SAN), timeout=120)
+        assert r.returncode == 0, (kind, r.stdout[-500:] + r.stderr[-2000:])
+        pieces[kind] = int(r.stdout.split()[1])
+    assert pieces["bytes ff"] == pieces["negative count"] == 0, pieces
+    assert R == 1 or (pieces["stray tiles"] > 0 and sum(pieces[k] for k in pieces if k.startswith("mix")) > 0), pieces
 
 
 @pytest.mark.parametrize("R,total_q,b,Hq,Hkv,d,max_kv,split", [

@@ -29,6 +29,8 @@ CASES = [
     (8, 8, 128, 64, 16, (64 * 13 - 16,) * 4, 0),       # 65 to 128 rows per kv-head, equal lengths
     (40, 1, 64, 64, 16, (500, 900), 0),                # whole-tile waves, three row blocks
     (4, 4, 128, 64, 4, (6000, 100, 64), 64),           # a given split: more items than workgroups
+    (100, 100, 64, 64, 4, (1800, 100, 700), 0),        # 11 ranges of 100 heads: more items than workgroups, claims
+    (150, 150, 128, 16, 2, (3000,), 0),                # 7 ranges of 150 heads
     (8, 8, 128, 64, 3, tuple(range(40, 40 + 63)), 0),  # 504 units: ranges
     (8, 8, 128, 64, 3, tuple(range(40, 40 + 64)), 0),  # 512 units: the list
 ]
