@@ -28,19 +28,27 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0  # MI355X HBM3E
-ATTN_SRC = os.path.join(ROOT, "paper_2607_25852_amd", "csrc", "attn.hip")
+CSRC = os.path.join(ROOT, "paper_2607_25852_amd", "csrc")
+# what decides the attention's traffic: both kernels, what they share, both plans, and the host's
+# choice between them with its split sizes
+ATTN_SOURCES = ("attn.hip", "attn_list.hip", "attn_list_plan.h", "attn_plan.h", "attn_tile.h", "rows.h", "sv_host.cpp",
+                "sv_host.h")
 # HBM traffic of one sv_verify_attn call, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs
-# scaled by a copy kernel of known size; valid only while the attention source is the
-# one that was measured (its digest is recorded beside the figure)
+# scaled by a copy kernel of known size; valid only while the attention sources are the
+# ones that were measured (their digest is recorded beside the figure)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sv_verify_attn_c64_b16_traffic.md")
 COPY_BYTES = 1 << 30  # copy-probe size: 1 GiB read + 1 GiB written, well above the 256 MB MALL
-ATTN_KERNELS = ("attn_plan_kernel", "attn_bf16_kernel", "attn_merge_kernel")
+# (plan, attention, merge) of each division of the attention's work; calls take one of them
+ATTN_DIVISIONS = {"ranges": ("attn_plan_kernel", "attn_bf16_kernel", "attn_merge_kernel"),
+                  "list": ("attn_list_plan_kernel", "attn_list_kernel", "attn_list_merge_kernel")}
+ATTN_KERNELS = tuple(k for names in ATTN_DIVISIONS.values() for k in names)
 ACCEPT_KERNELS = ("rowstats_kernel", "draw_kernel", "chunksum_kernel", "search_kernel")
-# per call kind: its kernels, the kernel dispatched once per call, where the bench records
-# the call's algorithmic bytes
+# per call kind: its kernels, the kernels one of which is dispatched once per call, where the
+# bench records the call's algorithmic bytes
 TRAFFIC_CALLS = {
-    "attention": (ATTN_KERNELS, "attn_bf16_kernel", ("roofline", "algorithmic_bytes")),
-    "acceptance": (ACCEPT_KERNELS, "rowstats_kernel", ("kernels", "acceptance_algorithmic_bytes")),
+    "attention": (ATTN_KERNELS, tuple(names[1] for names in ATTN_DIVISIONS.values()),
+                  ("roofline", "algorithmic_bytes")),
+    "acceptance": (ACCEPT_KERNELS, ("rowstats_kernel",), ("kernels", "acceptance_algorithmic_bytes")),
 }
 
 
@@ -50,8 +58,11 @@ def log(*a):
 
 def attn_source_digest():
     import hashlib
-    with open(ATTN_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for name in ATTN_SOURCES:
+        with open(os.path.join(CSRC, name), "rb") as f:
+            h.update(name.encode() + b"\0" + f.read())
+    return h.hexdigest()[:16]
 
 
 def recorded_traffic(workload):
@@ -94,14 +105,16 @@ def summarize_trace(stats_csv):
     for r in rows:
         out.append(f"| `{short_name(r['Name'])}` | {r['Calls']} | {float(r['AverageNs']) / 1e3:.1f} | "
                    f"{float(r['MinNs']) / 1e3:.1f} | {float(r['MaxNs']) / 1e3:.1f} | {float(r['Percentage']):.1f}% |")
-    run = [r for r in rows if "attn_bf16_kernel" in r["Name"] or "attn_merge_kernel" in r["Name"]]
-    if run:
+    for division, (plan_kernel, run_kernel, merge_kernel) in ATTN_DIVISIONS.items():
+        run = [r for r in rows if run_kernel in r["Name"] or merge_kernel in r["Name"]]
+        if not any(run_kernel in r["Name"] for r in run):
+            continue
         # average kernel time of one attention run (the persistent kernel and the merge); the
         # plan is built by its own kernel only where a call builds it (sv_verify_attn)
         tot = sum(float(r["AverageNs"]) for r in run) / 1e3
-        plan = [float(r["AverageNs"]) / 1e3 for r in rows if "attn_plan_kernel" in r["Name"]]
+        plan = [float(r["AverageNs"]) / 1e3 for r in rows if plan_kernel in r["Name"]]
         out.append("")
-        out.append(f"attention run per call (attention + merge kernels): {tot:.1f} us"
+        out.append(f"attention run per call ({division}: attention + merge kernels): {tot:.1f} us"
                    + (f"; plan kernel where a call builds its own plan: {plan[0]:.1f} us" if plan else ""))
     return "\n".join(out)
 
@@ -109,7 +122,7 @@ def summarize_trace(stats_csv):
 def summarize_traffic(fetch_dir, write_dir, call="attention"):
     """FETCH_SIZE / WRITE_SIZE per dispatch, scaled by the copy probe, as traffic per call
     of `call` (attention: sv_verify_attn; acceptance: sv_spec_accept)."""
-    kernels, main_kernel, alg_key = TRAFFIC_CALLS[call]
+    kernels, main_kernels, alg_key = TRAFFIC_CALLS[call]
     import csv
     import collections
 
@@ -138,7 +151,7 @@ def summarize_traffic(fetch_dir, write_dir, call="attention"):
             continue
         fv, wv = fetch.get(k, [0.0]), write.get(k, [0.0])
         out.append(f"| `{short_name(k)}` | {len(fv)} | {sum(fv) / len(fv):.0f} | {sum(wv) / len(wv):.0f} |")
-    main_calls = sum(len(v) for k, v in fetch.items() if main_kernel in k)
+    main_calls = sum(len(v) for k, v in fetch.items() if any(m in k for m in main_kernels))
     tf = sum(sum(v) for k, v in fetch.items() if any(a in k for a in kernels)) / main_calls
     tw = sum(sum(v) for k, v in write.items() if any(a in k for a in kernels)) / main_calls
     traffic = tf * 1024 * f_fetch + tw * 1024 * f_write
