@@ -87,7 +87,7 @@ __device__ inline uint64_t weight_of(float r) {
     return ((uint64_t)(uint32_t)hf << 32) | (uint64_t)(uint32_t)lf;
 }
 
-// Running sum of up to 2^12 weights floor(min(r, 1) * 2^40) as the sums of their upper 21 and
+// Running sum of fewer than 2^12 weights floor(min(r, 1) * 2^40) as the sums of their upper 21 and
 // lower 20 bits in two 32-bit registers: floor(r 2^20), and the remainder's next 20 bits (both
 // scalings are exact). Six vector operations a weight, where a 64-bit sum of weight_of takes ten;
 // the draw's chunk sums are bound by these at many requests.
@@ -102,6 +102,7 @@ struct WeightSum {
     }
     __device__ inline uint64_t total() const { return ((uint64_t)hi << 20) + lo; }
 };
+static_assert(kResPer < 1 << 12, "a thread's range of weights");
 
 template <typename T>
 __device__ inline const T* row_ptr(const void* base, long long row, int V) {

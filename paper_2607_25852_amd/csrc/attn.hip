@@ -15,11 +15,13 @@
 // A unit that lies in one range is written directly; the pieces of a cut unit leave fp32
 // partials merged by a second kernel (log-sum-exp weights).
 //
-// Bound by the K/V stream up to 64 rows per kv-head group and by the softmax's vector work in
-// whole-tile units; the rest is the pieces' starts and, with a list of splits, the uneven end.
-// Measured, the list of attn_list.hip against this: 4 requests of 4 positions (188 MB) 44.4 and
-// 40.3 us, 27 requests on pages of 16 tokens (256 MB) 65.1 and 53.0 us, 32 requests of
-// 65536..131072 tokens (6.45 GB) 1342 and 1251 us.
+// Bound by the K/V stream up to 64 rows per kv-head group, and in whole-tile units (above 128 rows)
+// by the chain of dependent steps in a tile (scores, maximum, exponents, PV), which keeps no unit
+// busy: at 32 requests of 65536..131072 tokens the matrix cores work 41% of the time, the vector
+// ALUs 40%, both at once 13%, neither 32%. The rest is the pieces' starts and, with a list of
+// splits, the uneven end. Measured, the list of attn_list.hip against this: 4 requests of 5
+// positions (188 MB) 44.7 and 40.1 us, 27 requests on pages of 16 tokens (256 MB) 65.1 and 53.4
+// us, 32 requests of 65536..131072 tokens (6.45 GB) 1353 and 1248 us.
 //
 // fp32 path (vector ALU): one workgroup per (query row, head); its four waves take
 // interleaved 64-key tiles and merge their softmax states at the end.

@@ -6,12 +6,20 @@
 // one (request, kv-head, row block), and persistent workgroups claim items, longest first, from a
 // counter. With several items per workgroup the claims even out the end by themselves, whatever
 // bounds an item. Below two units per compute unit the splits are too few or too short for that,
-// and ranges of equal cost are faster. Measured, this kernel against the ranges of attn.hip, 8
-// kv-heads: 64 requests of 512..32768 tokens and 16 positions 274 against 280 us, 128 requests of
-// 256..16384 tokens and 5 positions 261 against 270 us; 32 requests of 512..65536 tokens 298
-// against 275 us, 16 requests of 1024..8192 tokens 69 against 60 us.
-// Bound by the K/V stream: 1.70 GB in the first case, 6.2 TB/s over the call, of the 7.1 TB/s that
-// a plain read reaches.
+// and ranges of equal cost are faster. Measured, this kernel against the ranges of attn.hip
+// (contexts lognormal, two runs of each):
+//   256 units (32 requests, 8 kv-heads, pages of 64)   168 against 155 us
+//   384 units (48 requests)                            228-238 against 215
+//   512 units (64 requests)                            286-295 against 284-294
+//   768 units (96 requests, 5 positions)               390-397 against 400-432
+//   1024 units (128 requests, 5 positions)             273-278 against 276-291
+//   512 and 768 units of 4 kv-heads                    164-167 against 159-164, 229 against 227-236
+// On pages below 64 tokens, whose pages this kernel looks up per lane and the ranges per 1 KB
+// segment, the ranges are still ahead there: 512 units on pages of 16 309-313 against 299-300 us, at
+// head dim 64 166-168 against 155-158 us; 1024 units 310-314 against 311-313. The line is drawn by
+// units alone.
+// Bound by the K/V stream: at 64 requests of 512..32768 tokens and 16 positions 1.70 GB, 5.8 to 6.2
+// TB/s over the call on several cards, of the 7.1 TB/s that a plain read reaches.
 #include <algorithm>
 
 #include "attn_list_plan.h"

@@ -38,8 +38,8 @@ struct AttnArgs {
     float* part_lse;
     int R, total_q, Hq, Hkv, G, block;
     int log2P, maxp, num_pages, max_kv_len;
-    // list: tokens per split, most per request; nrb: row blocks per (request, kv-head). (In this
-    // order the list kernel keeps its arguments in scalar registers; spilled, it took 1% longer.)
+    // list: tokens per split, most per request; nrb: row blocks per (request, kv-head). (The order
+    // of the fields matters to the compiler: with others the list kernels took 1% longer.)
     int split, max_splits, nrb;
     int max_items;               // list: R * max_splits * Hkv * nrb (capped at INT_MAX)
     float scale_log2;  // sm_scale * log2(e)
