@@ -214,31 +214,46 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
         return p;
     }
     auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-    // A split size given by the caller, and two units per compute unit or more: a work list
-    // (attn_list.hip, with what either side measured). Its splits are each request's own, so that
-    // with a given size a request's results do not depend on the rest of the batch.
-    if (d.kv_split > 0 || (long long)d.num_reqs * d.num_kv_heads * p.row_blocks >= kAttnListUnits) {
+    // The list's split size: the caller's or, by default, about 8 work items per compute unit if
+    // every request had the longest context: R * Hkv * max_kv_len head-tokens over 256 CUs, divided
+    // by 8, at least 2048 tokens. Measured over split sizes 1024..24576, this picks the best or
+    // nearly the best one on 64 requests of up to 32768 tokens (8192) and of up to 65536 (16384):
+    // fewer, longer items save per-item prologues and merge work until the last items to finish
+    // start to dominate, and below 2048 tokens the per-item costs outweigh the extra parallelism.
+    // The host does not see the lengths themselves (they live on the device), so the bound uses
+    // max_kv_len.
+    int split = d.kv_split;
+    if (split <= 0) {
+        long long want = (long long)d.num_reqs * d.num_kv_heads * d.max_kv_len / (256 * 8);
+        if (want < 2048) want = 2048;
+        split = (int)(((want + 63) / 64) * 64);
+    }
+    if (split > d.max_kv_len) split = ((d.max_kv_len + 63) / 64) * 64;
+    // a split's page ids are staged in LDS: at most 1024 pages per split (a split of
+    // n tokens starting on a 64-token boundary touches at most n / P + 2 pages)
+    const long long max_split = 1022LL * d.page_size;
+    if (split > max_split) split = (int)(max_split / 64 * 64);
+    if (split < 64) split = 64;
+    // The list (attn_list.hip) is taken
+    // - for a split size given by the caller: its splits are each request's own, so that a request's
+    //   results do not depend on the rest of the batch;
+    // - from two units per compute unit on (measured in attn_list.hip);
+    // - where every request is one split, so that the list needs no merge kernel, and cuts would
+    //   cost more (6 us for each piece's start, 5 us for the merge) than the even end gives: up to
+    //   units / 8 tiles, or 9 where that is less. Over 1700 calls of 8 to 508 units, contexts up to
+    //   3000 tokens, 8 to 256 rows per unit, pages of 16 and 64, list against ranges: 32 requests of
+    //   500..1000 tokens, 16 positions 33 and 47 us, 16 requests of 16..60 tokens 15 and 22 us; above
+    //   the line 4 requests of 1000..2000 tokens 41 and 26 us. At most 12% slower than the better of
+    //   the two, 0.6% on average. (Fewer than 16 units, and more than 256 of at most 4 tiles and 64
+    //   rows, several of which a range takes without claims, are faster as ranges: 17 against 21 us
+    //   at 60 requests of 16..60 tokens.)
+    const long long units = (long long)d.num_reqs * d.num_kv_heads * p.row_blocks;
+    const int tiles = (int)(((long long)d.max_kv_len + 63) / 64);
+    const bool short_units = units >= 16 && split >= d.max_kv_len && tiles <= 32 &&
+                             8LL * tiles <= std::max<long long>(units, 72) &&
+                             !(units > kAttnItems && tiles <= 4 && maxM <= 64);
+    if (d.kv_split > 0 || units >= kAttnListUnits || short_units) {
         p.list = true;
-        int split = d.kv_split;
-        if (split <= 0) {
-            // About 8 work items per compute unit if every request had the longest context:
-            // R * Hkv * max_kv_len head-tokens over 256 CUs, divided by 8, at least 2048
-            // tokens. Measured over split sizes 1024..24576, this picks the best or nearly the
-            // best one on 64 requests of up to 32768 tokens (8192) and of up to 65536 (16384):
-            // fewer, longer items save per-item prologues and merge work until the last items to
-            // finish start to dominate, and below 2048 tokens the per-item costs outweigh the
-            // extra parallelism. The host does not see the lengths themselves (they live on the
-            // device), so the bound uses max_kv_len.
-            long long want = (long long)d.num_reqs * d.num_kv_heads * d.max_kv_len / (256 * 8);
-            if (want < 2048) want = 2048;
-            split = (int)(((want + 63) / 64) * 64);
-        }
-        if (split > d.max_kv_len) split = ((d.max_kv_len + 63) / 64) * 64;
-        // a split's page ids are staged in LDS: at most 1024 pages per split (a split of
-        // n tokens starting on a 64-token boundary touches at most n / P + 2 pages)
-        const long long max_split = 1022LL * d.page_size;
-        if (split > max_split) split = (int)(max_split / 64 * 64);
-        if (split < 64) split = 64;
         p.kv_split = split;
         p.max_splits = (d.max_kv_len + split - 1) / split;
         if (p.max_splits < 1) p.max_splits = 1;
@@ -258,10 +273,9 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
     const int hkv = d.num_kv_heads;
     int per_head = hkv <= kAttnItems ? kAttnItems / hkv : 0;
     if (per_head * hkv * 10 < kAttnItems * 9) per_head = (4 * kAttnItems + hkv - 1) / hkv;
-    const long long whole = ((long long)d.max_kv_len + 63) / 64 * 64;
-    p.kv_split = (int)whole;
+    p.kv_split = tiles * 64;
     p.max_splits = 1;
-    p.ranges = (int)std::min<long long>(per_head, (long long)d.num_reqs * p.row_blocks * (whole / 64));
+    p.ranges = (int)std::min<long long>(per_head, (long long)d.num_reqs * p.row_blocks * tiles);
     p.slot_rows = std::min(maxM, rows);
     // Two partial results per item: a unit that continues into it and one that starts there. A plan
     // of one range has no cuts, but a run on a workspace without a plan may find some.

@@ -148,6 +148,32 @@ int main() {
         check_attn_layout(d);
     }
     count(sv::check_attn(nullptr));
+    // which division of the attention's work a call takes, on either side of each line
+    {
+        struct Line { int reqs, hq, hkv, block, page, kv, split; bool list; };
+        const Line lines[] = {
+            {64, 64, 8, 16, 64, 1 << 17, 0, true},   {63, 64, 8, 16, 64, 1 << 17, 0, false},  // 512 units
+            {4, 64, 8, 5, 64, 1 << 17, 4096, true},  {4, 64, 8, 5, 64, 1 << 17, 0, false},    // a given split
+            {2, 64, 8, 5, 64, 64 * 9, 0, true},      {2, 64, 8, 5, 64, 64 * 9 + 1, 0, false}, // short units
+            {1, 64, 8, 5, 64, 64, 0, false},         {16, 64, 8, 16, 64, 64 * 16, 0, true},
+            {16, 64, 8, 16, 64, 64 * 16 + 1, 0, false}, {32, 64, 8, 16, 64, 2048, 0, true},
+            {32, 64, 8, 16, 64, 2049, 0, false},     {60, 64, 8, 16, 64, 2049, 0, false},
+            {33, 64, 8, 5, 64, 64 * 4, 0, false},    {33, 64, 8, 5, 64, 64 * 4 + 1, 0, true},
+            {33, 64, 8, 16, 64, 64 * 4, 0, true},    {32, 64, 8, 5, 64, 64 * 4, 0, true},
+            {32, 64, 8, 5, 1, 960, 0, true},         {32, 64, 8, 5, 1, 961, 0, false},        // 1022 pages a split
+        };
+        for (const Line& l : lines) {
+            sv_attn_desc d{};
+            d.num_reqs = l.reqs; d.total_q_max = l.reqs * l.block; d.block = l.block; d.num_q_heads = l.hq;
+            d.num_kv_heads = l.hkv; d.head_dim = 128; d.page_size = l.page; d.max_pages_per_req = 1 << 17;
+            d.num_pages = 1 << 20; d.max_kv_len = l.kv; d.dtype = SV_BF16; d.kv_split = l.split;
+            expect(sv::check_attn(&d) == SV_OK, "a call on the line is accepted");
+            const sv::AttnPlan p = sv::plan_attn(d);
+            if (p.list != l.list) std::fprintf(stderr, "%d requests, %d keys, split %d: ", l.reqs, l.kv, l.split);
+            expect(p.list == l.list, "the division of the work");
+            check_attn_layout(d);
+        }
+    }
     // acceptance
     for (int it = 0; it < 200000; it++) {
         sv_accept_desc d{};

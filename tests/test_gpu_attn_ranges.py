@@ -3,7 +3,7 @@
 Ranges of equal cost: head counts that do not divide the compute units, pages that hold a whole
 tile, a DMA segment of one or less, contexts of more pages than are staged at once, cuts at and
 next to the ends of units, more items than workgroups, and several row blocks. The work list:
-the first size that takes it, next to the last one that does not. Gates of test_gpu_attn.py.
+the first sizes that take it, next to the last ones that do not. Gates of test_gpu_attn.py.
 """
 import dataclasses
 
@@ -29,8 +29,17 @@ CASES = [
     (8, 8, 128, 64, 16, (64 * 13 - 16,) * 4, 0),       # 65 to 128 rows per kv-head, equal lengths
     (40, 1, 64, 64, 16, (500, 900), 0),                # whole-tile waves, three row blocks
     (4, 4, 128, 64, 4, (6000, 100, 64), 64),           # a given split: more items than workgroups
-    (100, 100, 64, 64, 4, (1800, 100, 700), 0),        # 11 ranges of 100 heads: more items than workgroups, claims
+    (100, 100, 64, 64, 4, (2300, 100, 700), 0),        # 11 ranges of 100 heads: more items than workgroups, claims
     (150, 150, 128, 16, 2, (3000,), 0),                # 7 ranges of 150 heads
+    (16, 4, 128, 64, 4, (64 * 9 - 4, 40, 200, 333), 0),     # 16 units of at most 9 tiles: the list, one split each
+    (16, 4, 128, 64, 4, (64 * 9 - 3, 40, 200, 333), 0),     # 10 tiles: ranges
+    (64, 8, 128, 64, 16, (64 * 9, 7, 500, 90), 0),          # 32 units, 65 to 128 rows, 10 tiles: ranges
+    (32, 8, 64, 16, 8, (64 * 16 - 8,) + (300,) * 15, 0),    # 128 units of at most 16 tiles: the list
+    (32, 8, 64, 16, 8, (64 * 16 - 7,) + (300,) * 15, 0),    # 17 tiles: ranges
+    (32, 2, 128, 64, 16, (64 * 9 - 16,) + (100,) * 7, 0),   # 16 units of whole-tile waves: the list
+    (16, 8, 128, 64, 4, (64 * 4 - 4,) + (60,) * 32, 0),     # 264 units of at most 4 tiles: ranges
+    (16, 8, 128, 64, 4, (64 * 4 - 3,) + (60,) * 32, 0),     # 5 tiles: the list
+    (4, 4, 64, 1, 4, (1100,) + (50,) * 39, 0),              # 160 units, two splits on pages of one token: ranges
     (8, 8, 128, 64, 3, tuple(range(40, 40 + 63)), 0),  # 504 units: ranges
     (8, 8, 128, 64, 3, tuple(range(40, 40 + 64)), 0),  # 512 units: the list
 ]
