@@ -169,7 +169,10 @@ __device__ __forceinline__ float2 chunk_stats(const T* row, int beg, int end, in
         const typename Vec<T>::unaligned* rv = (const typename Vec<T>::unaligned*)(row + beg);
         typename Vec<T>::type v[kStatsLoads];
 #pragma unroll
-        for (int k = 0; k < kStatsLoads; k++) v[k] = stream_load<T>(rv + tid + k * kThreads);
+        for (int k = 0; k < kStatsLoads; k++) {
+            v[k] = stream_load<T>(rv + tid + k * kThreads);
+            __builtin_amdgcn_sched_barrier(0);  // (in this order, and no conversion that waits in between)
+        }
 #pragma unroll
         for (int k = 0; k < kStatsLoads; k++)
 #pragma unroll

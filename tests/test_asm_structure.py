@@ -155,3 +155,19 @@ def test_vector_loads_keep_their_alignment(tmp_path):
     for name, body in _functions(_assemble("accept.hip", tmp_path)):
         if re.search(r"rowstats_kernel|argmax_kernel|dstats_chunk_kernel", name):
             assert sum("global_load_dwordx4" in l and " nt" in l for l in body) >= 8, name
+
+
+def test_chunk_loads_are_in_flight_together(tmp_path):
+    """The statistics passes issue a chunk's four 16-byte loads back to back: no wait between them,
+    which would make two round trips to memory of one."""
+    seen = 0
+    for name, body in _functions(_assemble("accept.hip", tmp_path)):
+        if not re.search(r"rowstats_kernel|dstats_chunk_kernel", name):
+            continue
+        seen += 1
+        at = [i for i, l in enumerate(body) if "global_load_dwordx4" in l and " nt" in l]
+        assert len(at) % 4 == 0, (name, len(at))
+        for g in range(0, len(at), 4):
+            between = body[at[g]:at[g + 3]]
+            assert not any("s_waitcnt" in l and "vmcnt" in l for l in between), (name, between)
+    assert seen == 4, seen
