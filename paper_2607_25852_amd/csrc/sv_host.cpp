@@ -252,7 +252,16 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
     const bool short_units = units >= 16 && split >= d.max_kv_len && tiles <= 32 &&
                              8LL * tiles <= std::max<long long>(units, 72) &&
                              !(units > kAttnItems && tiles <= 4 && maxM <= 64);
-    if (d.kv_split > 0 || units >= kAttnListUnits || short_units) {
+    // - where the heads divide the compute units badly: ranges then need about four items per
+    //   compute unit and claims of their own, and are faster in few units of short contexts only. 44
+    //   to 200 kv-heads, list against ranges: 0.82 to 1.0 times the time above 112 units or 4096
+    //   tokens (4 requests of 96 heads, 20000..40000 tokens, 0.91 to 0.97), 1.05 to 1.8 below.
+    const int hkv = d.num_kv_heads;
+    int per_head = hkv <= kAttnItems ? kAttnItems / hkv : 0;
+    const bool uneven = per_head * hkv * 10 < kAttnItems * 9;
+    if (uneven) per_head = (4 * kAttnItems + hkv - 1) / hkv;
+    const bool uneven_list = uneven && (units > 112 || tiles > 64);
+    if (d.kv_split > 0 || units >= kAttnListUnits || short_units || uneven_list) {
         p.list = true;
         p.kv_split = split;
         p.max_splits = (d.max_kv_len + split - 1) / split;
@@ -270,9 +279,6 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
     // together one item per compute unit (no more than the longest contexts hold tiles). Head
     // counts that would leave over a tenth of the compute units without an item get about four
     // items per unit.
-    const int hkv = d.num_kv_heads;
-    int per_head = hkv <= kAttnItems ? kAttnItems / hkv : 0;
-    if (per_head * hkv * 10 < kAttnItems * 9) per_head = (4 * kAttnItems + hkv - 1) / hkv;
     p.kv_split = tiles * 64;
     p.max_splits = 1;
     p.ranges = (int)std::min<long long>(per_head, (long long)d.num_reqs * p.row_blocks * tiles);

@@ -160,6 +160,9 @@ int main() {
             {32, 64, 8, 16, 64, 2049, 0, false},     {60, 64, 8, 16, 64, 2049, 0, false},
             {33, 64, 8, 5, 64, 64 * 4, 0, false},    {33, 64, 8, 5, 64, 64 * 4 + 1, 0, true},
             {33, 64, 8, 16, 64, 64 * 4, 0, true},    {32, 64, 8, 5, 64, 64 * 4, 0, true},
+            {1, 112, 112, 5, 64, 4096, 0, false},    {1, 112, 112, 5, 64, 4097, 0, true},     // uneven heads
+            {2, 56, 56, 5, 64, 4096, 0, false},      {1, 113, 113, 5, 64, 4096, 0, true},
+            {2, 40, 40, 5, 64, 1 << 17, 0, false},   {1, 128, 128, 5, 64, 1 << 17, 0, false},
             {32, 64, 8, 5, 1, 960, 0, true},         {32, 64, 8, 5, 1, 961, 0, false},        // 1022 pages a split
         };
         for (const Line& l : lines) {

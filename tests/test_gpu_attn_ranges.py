@@ -29,8 +29,11 @@ CASES = [
     (8, 8, 128, 64, 16, (64 * 13 - 16,) * 4, 0),       # 65 to 128 rows per kv-head, equal lengths
     (40, 1, 64, 64, 16, (500, 900), 0),                # whole-tile waves, three row blocks
     (4, 4, 128, 64, 4, (6000, 100, 64), 64),           # a given split: more items than workgroups
-    (100, 100, 64, 64, 4, (2300, 100, 700), 0),        # 11 ranges of 100 heads: more items than workgroups, claims
-    (150, 150, 128, 16, 2, (3000,), 0),                # 7 ranges of 150 heads
+    (100, 100, 64, 64, 4, (2300,), 0),                 # 11 ranges of 100 heads: more items than workgroups, claims
+    (56, 56, 128, 16, 2, (3000, 700), 0),              # 19 ranges of 56 heads, 112 units
+    (57, 57, 128, 16, 2, (3000, 700), 0),              # 114 units of an uneven head count: the list
+    (44, 44, 64, 64, 2, (4090,), 0),                   # 64 tiles: ranges
+    (44, 44, 64, 64, 2, (4100,), 0),                   # 65 tiles: the list, three splits
     (16, 4, 128, 64, 4, (64 * 9 - 4, 40, 200, 333), 0),     # 16 units of at most 9 tiles: the list, one split each
     (16, 4, 128, 64, 4, (64 * 9 - 3, 40, 200, 333), 0),     # 10 tiles: ranges
     (64, 8, 128, 64, 16, (64 * 9, 7, 500, 90), 0),          # 32 units, 65 to 128 rows, 10 tiles: ranges
