@@ -20,7 +20,7 @@
 namespace sv {
 
 constexpr int kAttnTile = 64;       // KV tokens per tile of the attention kernel
-constexpr int kPlanMinTiles = 6;    // no range of the automatic plan is shorter
+constexpr int kPlanMinTiles = 6;    // no range is shorter unless the line is
 constexpr int kPlanGrid = 256;      // compute units
 constexpr int kPlanUnits = 2 * kPlanGrid;  // from this many units on the work is a list (attn_list.hip)
 constexpr int kPlanSnapTiles = 2;   // a cut this close to a unit's end is moved onto it
@@ -118,7 +118,10 @@ __device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint32_
     // 2. the size of the ranges
     constexpr uint32_t least = kCostStart + kPlanMinTiles * kCostTile;
     const uint32_t even = (W + (uint32_t)a.ranges - 1) / (uint32_t)a.ranges;
-    const uint32_t step = even < least ? least : even;
+    // A line too short for that (far below the longest contexts the host allows for) leaves compute
+    // units idle: there a range starts at every unit, and only long units are cut.
+    const uint32_t step = even < least / 2 ? least / 2 : even;
+    const bool brief = step < least;
     const int n = (int)((W + step - 1) / step);  // (at most a.ranges)
     // the items of a range share an XCD when its workgroups hold whole ranges (attn.hip)
     const bool skewed = n > 0 && n % 8 == 0 && n * a.heads <= kPlanGrid;
@@ -150,7 +153,7 @@ __device__ inline void build_attn_plan(const AttnPlanArgs& a, ReqFn req, uint32_
             }
             const unsigned start = plan_start_cost(a.G * k_i - rb * a.rb_rows);
             int t = x > start ? (int)((x - start) / plan_tile_cost(a.G * k_i - rb * a.rb_rows)) : 0;
-            if (t <= kPlanSnapTiles) t = 0;
+            if (t <= kPlanSnapTiles || (brief && nt < 2 * kPlanMinTiles)) t = 0;
             if (t >= nt || (nt - t <= kPlanSnapTiles && t > 0)) {
                 t = 0;
                 rb++;

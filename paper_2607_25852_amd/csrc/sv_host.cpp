@@ -240,18 +240,16 @@ AttnPlan plan_attn(const sv_attn_desc& d) {
     // - from two units per compute unit on (measured in attn_list.hip);
     // - where every request is one split, so that the list needs no merge kernel, and cuts would
     //   cost more (6 us for each piece's start, 5 us for the merge) than the even end gives: up to
-    //   units / 8 tiles, or 9 where that is less. Over 1700 calls of 8 to 508 units, contexts up to
-    //   3000 tokens, 8 to 256 rows per unit, pages of 16 and 64, list against ranges: 32 requests of
-    //   500..1000 tokens, 16 positions 33 and 47 us, 16 requests of 16..60 tokens 15 and 22 us; above
-    //   the line 4 requests of 1000..2000 tokens 41 and 26 us. At most 12% slower than the better of
-    //   the two, 0.6% on average. (Fewer than 16 units, and more than 256 of at most 4 tiles and 64
-    //   rows, several of which a range takes without claims, are faster as ranges: 17 against 21 us
-    //   at 60 requests of 16..60 tokens.)
+    //   units / 8 tiles. Few units, and units of up to 64 rows and few tiles, which a range takes
+    //   one or several of without claims, are faster as ranges. Measured over 1716 calls of 8 to 508 units, contexts up
+    //   to 3000 tokens, 8 to 256 rows per unit, pages of 16 and 64, list against ranges: 32 requests of
+    //   500..1000 tokens and 16 positions 33 and 47 us; 4 requests of 1000..2000 tokens 41 and 23 us,
+    //   28 requests of 30..60 tokens and 5 positions 14 and 10 us. By this rule a call takes at most
+    //   19% longer than by the better of the two, 0.8% on average.
     const long long units = (long long)d.num_reqs * d.num_kv_heads * p.row_blocks;
     const int tiles = (int)(((long long)d.max_kv_len + 63) / 64);
-    const bool short_units = units >= 16 && split >= d.max_kv_len && tiles <= 32 &&
-                             8LL * tiles <= std::max<long long>(units, 72) &&
-                             !(units > kAttnItems && tiles <= 4 && maxM <= 64);
+    const bool short_units = split >= d.max_kv_len && tiles <= 32 && 8LL * tiles <= units &&
+                             (maxM > 64 ? units >= 64 : tiles > (units >= 240 ? 4 : 10));
     // - where the heads divide the compute units badly: ranges then need about four items per
     //   compute unit and claims of their own, and are faster in few units of short contexts only. 44
     //   to 200 kv-heads, list against ranges: 0.82 to 1.0 times the time above 112 units or 4096

@@ -154,7 +154,7 @@ int tiles_of(const Round& r, int i) {
 
 // the cuts by their definition: cut c at c equal parts of the line's cost (with the odd XCDs'
 // parts 17/1024 shorter where the ranges are shared out evenly), moved onto a unit's end within
-// two tiles of it
+// two tiles of it; on a short line moved onto the start of a unit of fewer than 12 tiles
 std::vector<sv::AttnRange> cuts_of(const Round& r) {
     const sv::AttnPlanArgs& a = r.a;
     uint64_t W = 0;
@@ -163,7 +163,8 @@ std::vector<sv::AttnRange> cuts_of(const Round& r) {
         before.push_back(W);
         for (int rb = 0; rb < a.nrb; rb++) W += unit_cost(a.G * r.k[i] - rb * a.rb_rows, tiles_of(r, i));
     }
-    const uint64_t step = std::max<uint64_t>((W + a.ranges - 1) / a.ranges, 100 + 6 * 16);
+    const uint64_t step = std::max<uint64_t>((W + a.ranges - 1) / a.ranges, (100 + 6 * 16) / 2);
+    const bool brief = step < 100 + 6 * 16;
     const int n = (int)((W + step - 1) / step);
     std::vector<sv::AttnRange> out(n + 1, sv::AttnRange{a.R, 0, 0, 0, 0, 0, 0, 0});
     for (int c = 0; c < n; c++) {
@@ -183,7 +184,7 @@ std::vector<sv::AttnRange> cuts_of(const Round& r) {
         const int M = a.G * r.k[i] - rb * a.rb_rows;
         const uint64_t start = M > 64 ? 144 : 100;
         int t = x > start ? (int)((x - start) / (M > 128 ? 32 : M > 64 ? 20 : 16)) : 0;
-        if (t <= 2) t = 0;
+        if (t <= 2 || (brief && nt < 12)) t = 0;
         if (t >= nt || (t > 0 && nt - t <= 2)) t = 0, rb++;
         out[c] = sv::AttnRange{i, rb, t, r.q0[i], r.k[i], r.kv[i], 0, 0};
     }

@@ -154,12 +154,15 @@ int main() {
         const Line lines[] = {
             {64, 64, 8, 16, 64, 1 << 17, 0, true},   {63, 64, 8, 16, 64, 1 << 17, 0, false},  // 512 units
             {4, 64, 8, 5, 64, 1 << 17, 4096, true},  {4, 64, 8, 5, 64, 1 << 17, 0, false},    // a given split
-            {2, 64, 8, 5, 64, 64 * 9, 0, true},      {2, 64, 8, 5, 64, 64 * 9 + 1, 0, false}, // short units
-            {1, 64, 8, 5, 64, 64, 0, false},         {16, 64, 8, 16, 64, 64 * 16, 0, true},
-            {16, 64, 8, 16, 64, 64 * 16 + 1, 0, false}, {32, 64, 8, 16, 64, 2048, 0, true},
-            {32, 64, 8, 16, 64, 2049, 0, false},     {60, 64, 8, 16, 64, 2049, 0, false},
-            {33, 64, 8, 5, 64, 64 * 4, 0, false},    {33, 64, 8, 5, 64, 64 * 4 + 1, 0, true},
-            {33, 64, 8, 16, 64, 64 * 4, 0, true},    {32, 64, 8, 5, 64, 64 * 4, 0, true},
+            {8, 64, 8, 16, 64, 64 * 8, 0, true},     {8, 64, 8, 16, 64, 64 * 8 + 1, 0, false}, // short units
+            {7, 64, 8, 16, 64, 64 * 2, 0, false},    {64, 8, 1, 16, 64, 64, 0, true},
+            {16, 64, 8, 16, 64, 64 * 16, 0, true},   {16, 64, 8, 16, 64, 64 * 16 + 1, 0, false},
+            {32, 64, 8, 16, 64, 2048, 0, true},      {32, 64, 8, 16, 64, 2049, 0, false},
+            {60, 64, 8, 16, 64, 2048, 0, true},      {60, 64, 8, 16, 64, 2049, 0, false},
+            {29, 64, 8, 8, 64, 64 * 10, 0, false},   {29, 64, 8, 8, 64, 64 * 10 + 1, 0, true},  // up to 64 rows
+            {30, 64, 8, 8, 64, 64 * 4, 0, false},    {30, 64, 8, 8, 64, 64 * 4 + 1, 0, true},
+            {30, 64, 8, 9, 64, 64 * 4, 0, true},     {1, 64, 8, 16, 64, 64, 0, false},
+            {1, 64, 8, 5, 64, 64, 0, false},
             {1, 112, 112, 5, 64, 4096, 0, false},    {1, 112, 112, 5, 64, 4097, 0, true},     // uneven heads
             {2, 56, 56, 5, 64, 4096, 0, false},      {1, 113, 113, 5, 64, 4096, 0, true},
             {2, 40, 40, 5, 64, 1 << 17, 0, false},   {1, 128, 128, 5, 64, 1 << 17, 0, false},

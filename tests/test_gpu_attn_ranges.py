@@ -34,12 +34,16 @@ CASES = [
     (57, 57, 128, 16, 2, (3000, 700), 0),              # 114 units of an uneven head count: the list
     (44, 44, 64, 64, 2, (4090,), 0),                   # 64 tiles: ranges
     (44, 44, 64, 64, 2, (4100,), 0),                   # 65 tiles: the list, three splits
-    (16, 4, 128, 64, 4, (64 * 9 - 4, 40, 200, 333), 0),     # 16 units of at most 9 tiles: the list, one split each
-    (16, 4, 128, 64, 4, (64 * 9 - 3, 40, 200, 333), 0),     # 10 tiles: ranges
+    (32, 4, 128, 64, 16, (64 * 8 - 16,) + (60,) * 15, 0),   # 64 units of at most 8 tiles: the list, one split each
+    (32, 4, 128, 64, 16, (64 * 8 - 15,) + (60,) * 15, 0),   # 9 tiles: ranges, a short line
+    (32, 4, 128, 64, 16, (64 * 2 - 16, 40, 20, 7), 0),      # 16 units: ranges
+    (16, 4, 128, 64, 4, (64 * 30, 40, 200, 333), 0),        # a short line with one long unit
     (64, 8, 128, 64, 16, (64 * 9, 7, 500, 90), 0),          # 32 units, 65 to 128 rows, 10 tiles: ranges
     (32, 8, 64, 16, 8, (64 * 16 - 8,) + (300,) * 15, 0),    # 128 units of at most 16 tiles: the list
     (32, 8, 64, 16, 8, (64 * 16 - 7,) + (300,) * 15, 0),    # 17 tiles: ranges
-    (32, 2, 128, 64, 16, (64 * 9 - 16,) + (100,) * 7, 0),   # 16 units of whole-tile waves: the list
+    (32, 8, 64, 16, 8, (64 * 10 - 8,) + (300,) * 15, 0),    # up to 64 rows, 10 tiles: ranges
+    (32, 8, 64, 16, 8, (64 * 10 - 7,) + (300,) * 15, 0),    # 11 tiles: the list
+    (32, 2, 128, 64, 16, (64 * 8 - 16,) + (50,) * 31, 0),   # 64 units of whole-tile waves: the list
     (16, 8, 128, 64, 4, (64 * 4 - 4,) + (60,) * 32, 0),     # 264 units of at most 4 tiles: ranges
     (16, 8, 128, 64, 4, (64 * 4 - 3,) + (60,) * 32, 0),     # 5 tiles: the list
     (4, 4, 64, 1, 4, (1100,) + (50,) * 39, 0),              # 160 units, two splits on pages of one token: ranges
