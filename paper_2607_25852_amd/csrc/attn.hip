@@ -1,19 +1,17 @@
 // Verify attention over a paged KV cache (AngelSpec Sec. 4.1: every kept block
 // position is evaluated by the target model; Sec. 4.2: one dense packed batch).
 //
-// bf16 path (MFMA), for fewer than two (request, kv-head, row block) units per compute unit and no
-// given split size; from there on a list of items does as well or better (attn_list.hip). The plan
+// bf16 path (MFMA), for the calls of few (request, kv-head, row block) units that the host does not
+// give to the list of items in attn_list.hip (plan_attn, with what either side measured). The plan
 // (attn_plan.h) cuts the line of all (request, row block) units of a kv-head into ranges by cost;
 // a workgroup takes one range of one head at a time and processes its pieces: the query rows of a
 // unit against a run of 64-token tiles of the request's context. Query rows go on the N side of
 // the MFMA and KV tokens on the M side, so S^T = K Q^T puts all scores of one query row in one
-// lane pair:
-// the online-softmax max/sum is lane-local plus one cross-half swap. The P^T
-// fragment is then already in the B-operand layout of O^T = V^T P^T; V is staged
-// transposed in LDS to serve the A operand. K and V tiles of 64 tokens are
-// gathered through the page table into an LDS ring while earlier tiles are multiplied.
-// A unit that lies in one range is written directly; the pieces of a cut unit leave fp32
-// partials merged by a second kernel (log-sum-exp weights).
+// lane pair: the online-softmax max/sum is lane-local plus one cross-half swap. The P^T fragment
+// is then already in the B-operand layout of O^T = V^T P^T; V is staged transposed in LDS to
+// serve the A operand. K and V tiles of 64 tokens are gathered through the page table into an LDS
+// ring while earlier tiles are multiplied. A unit that lies in one range is written directly; the
+// pieces of a cut unit leave fp32 partials merged by a second kernel (log-sum-exp weights).
 //
 // Bound by the K/V stream up to 64 rows per kv-head group, and in whole-tile units (above 128 rows)
 // by the chain of dependent steps in a tile (scores, maximum, exponents, PV), which keeps no unit

@@ -1,6 +1,6 @@
-// Verify attention over a paged KV cache for calls of many units, bf16: at least two (request,
-// kv-head, row block) units per compute unit; and for calls with a given split size, whose splits
-// are each request's own.
+// Verify attention over a paged KV cache, bf16, over a list of items: for calls of at least two
+// (request, kv-head, row block) units per compute unit, for calls with a given split size, whose
+// splits are each request's own, and for calls of short contexts (plan_attn).
 //
 // The same products as in attn.hip, over another division of the work: an item is one split of
 // one (request, kv-head, row block), and persistent workgroups claim items, longest first, from a

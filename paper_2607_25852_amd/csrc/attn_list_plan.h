@@ -1,11 +1,10 @@
-// Work list of the persistent verify-attention kernel for calls of many units or with a given
-// split size (attn_list.hip), built by one workgroup. Every (request, split) group is bucketed by its tile count: full splits share the top bucket,
-// a request's shorter last split lands in the bucket of its own length. The buckets are
-// laid out in decreasing size (a counting sort), so the persistent workgroups take the
-// long items early and the short ones fill the tail. The order inside a bucket is
-// unspecified and does not affect any result: every item writes its own output rows or
-// partial slot. Used by the attention call's own plan kernel and by the round set-up
-// kernel (sv_prepare_round), so both build the same list.
+// Work list of the verify attention over a list of items (attn_list.hip), built by one workgroup.
+// Every (request, split) group is bucketed by its tile count: full splits share the top bucket, a
+// request's shorter last split lands in the bucket of its own length. The buckets are laid out in
+// decreasing size (a counting sort), so the persistent workgroups take the long items early and
+// the short ones fill the tail. The order inside a bucket is unspecified and does not affect any
+// result: every item writes its own output rows or partial slot. Used by the attention call's own
+// plan kernel and by the round set-up kernel (sv_prepare_round), so both build the same list.
 #pragma once
 #include <hip/hip_runtime.h>
 

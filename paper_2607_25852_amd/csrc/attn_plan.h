@@ -28,7 +28,7 @@ constexpr int kPlanSnapTiles = 2;   // a cut this close to a unit's end is moved
 // (bound by its K/V stream): its start and end (descriptors, page ids, queries, the first
 // tile's latency, the merge of the token halves: 6.3 us, 9.8 us above 64 rows) and its tiles.
 // Above 64 rows the tile's matrix and vector work shows (1.3 against 1.05 us), and above 128
-// rows (whole-tile waves) it bounds the tile (1.9 us).
+// rows (whole-tile waves) the chain of dependent steps bounds the tile (1.9 us).
 constexpr unsigned kCostStart = 100, kCostStart65 = 144, kCostTile = 16, kCostTile65 = 20, kCostWideTile = 32;
 // Workgroups on the odd XCDs end 3 to 4% later than those on the even ones with the same work
 // (attention over 188 MB to 6.4 GB, several cards), so their ranges are this many 1024ths

@@ -29,7 +29,7 @@ struct ReqPlan {
 constexpr int kAttnItems = 256;  // items of the automatic attention plan: one per compute unit
 constexpr int kAttnListUnits = 2 * kAttnItems;  // (request, kv-head, row block) units that take the list
 struct AttnPlan {
-    bool list;        // a list of items (many units or a given split, attn_list.hip), else ranges of equal cost (attn.hip)
+    bool list;        // a list of items (attn_list.hip), else ranges of equal cost (attn.hip)
     int kv_split;     // list: tokens per work item, the caller's or chosen; ranges: the longest context
     int max_splits;   // ceil(max_kv_len / kv_split)
     int waves;        // waves per workgroup (bf16 path)
